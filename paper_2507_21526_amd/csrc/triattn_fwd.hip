@@ -85,8 +85,11 @@ struct FwdArgs {
     int32_t n_slots;
     int32_t upw;
     // single-unit kernel: the first n_lead items (a Triangle schedule's Last
-    // split items) are interleaved with the others in launch order (0: none)
+    // split items) are spread over the first lead_span launch slots (n_lead
+    // <= lead_span <= n_items), between the others (0: launch order is
+    // schedule order)
     int32_t n_lead;
+    int32_t lead_span;
 };
 
 struct MergeArgs {
@@ -345,14 +348,15 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void attn_tile_kernel(Fwd
     int item = bid / a.subtiles;
     if (item >= a.n_items)
         return;
-    if (a.n_lead > 0) {
-        // Launch slot x runs lead item floor(x n_lead / n_items) when that
+    if (item < a.lead_span) {
+        // Launch slot x runs lead item floor(x n_lead / lead_span) when that
         // count steps up at x, else the next of the other items: the lead
         // items (Last splits, each a run of k-tiles along the sequence) are
-        // spread evenly through the launch, each beside the streaming q-tiles
-        // whose bands have just read its keys into L2, instead of all reading
-        // K and V from HBM at the start.  A bijection on [0, n_items).
-        const uint32_t x = (uint32_t)item, nl = (uint32_t)a.n_lead, ni = (uint32_t)a.n_items;
+        // spread through the launch, each beside the streaming q-tiles whose
+        // bands have just read its keys into L2, instead of all reading K and
+        // V from HBM at the start.  Slots past lead_span run the item of
+        // their own index.  A bijection on [0, n_items).
+        const uint32_t x = (uint32_t)item, nl = (uint32_t)a.n_lead, ni = (uint32_t)a.lead_span;
         const uint32_t s0 = x * nl / ni, s1 = (x + 1) * nl / ni;
         item = s1 > s0 ? (int)s0 : (int)(nl + x - s1);
     }
@@ -2330,12 +2334,68 @@ FwdArgs make_args(const void *q, const void *k, const void *v, void *o,
     a.n_units = 0;
     a.n_slots = 0;
     a.upw = 1;
-    // Triangle schedules interleave their Last split items into the launch
-    // (the slot arithmetic is 32-bit unsigned: (n_items + 1) n_lead < 2^32)
-    const bool lead_fits = (uint64_t)(info->n_items + 1) * (uint64_t)info->n_last_items <
-                           ((uint64_t)1 << 32);
-    a.n_lead = info->kind == TA_KIND_TRIANGLE && lead_fits ? info->n_last_items : 0;
+    a.n_lead = 0;
+    a.lead_span = 0;
     return a;
+}
+
+// Device time of a launch, in units of 1000 cycles at d = 128, for choosing
+// between forms and orders of it: workgroups of `slots` at a time, each with
+// a fixed cost (schedule item, Q and the first K tile from memory, pipeline
+// fill, epilogue) and a cost per 64-key step; the longest bounds the pass
+// from below, and a pass of several rounds ends half a workgroup late on
+// average.
+struct LaunchCost {
+    double fixed, step, slots;
+    double wg(double steps) const { return fixed + step * steps; }
+    double pass(double wgs, double mean_steps, double max_steps) const
+    {
+        const double all = wgs > slots ? (wgs / slots + 0.5) * wg(mean_steps) : 0.0;
+        return std::max(wg(max_steps), all);
+    }
+};
+// Workgroups of at most four waves run two to a CU, at nearly the speed of
+// one each.
+LaunchCost tile_cost(int nw)
+{
+    return nw <= 4 ? LaunchCost{10.0, 2.6, 512.0} : LaunchCost{10.0, 2.4, 256.0};
+}
+
+// Launch slots over which a Triangle schedule's Last split items are spread
+// (FwdArgs::lead_span).  Spread evenly over the whole launch each split finds
+// its keys in L2 (HBM traffic of a 128K layer 2.87 instead of 3.36 GB; the
+// multi-head layer at 96K tokens is 6 % faster than with the splits first),
+// but one that starts in the last round runs on alone: a split has 32 steps
+// or more, a streaming item at window 512 ten.  So the last of them starts
+// where the time left is that of one split: at 6000 tokens and window 512
+// (32 heads over 8 kv heads) the launch takes 89 instead of 115 us, at 12000
+// tokens 156 instead of 180.  A split that starts early no longer meets its
+// keys in L2, so a launch whose tail is short against it keeps the even
+// spread: under 0.15 of it (48000 tokens, window 300 or 512: from 5 % slower to
+// 10 % faster moved, with the place); under 0.3 for workgroups of at most four waves,
+// whose K and V copies serve half the rows (multi-head, 12000 tokens: window
+// 2048 1 % slower moved, window 512 4 % faster).  So does one whose splits
+// are not much longer than its streaming items (multi-head, 3000 tokens,
+// window 2048: 8 % slower moved).
+int32_t lead_slots(const FwdArgs &a, const ta_schedule_info *info, int nw, int64_t wgs)
+{
+    // the slot arithmetic is 32-bit unsigned: (n_items + 1) n_lead < 2^32
+    const uint64_t n = (uint64_t)info->n_items, nl = (uint64_t)info->n_last_items;
+    if (info->kind != TA_KIND_TRIANGLE || nl == 0 || nl > n || (n + 1) * nl >= (1ull << 32))
+        return 0;
+    const double T = info->tile;  // most k-tiles of a streaming item, as the builder sizes them
+    const double streaming = std::ceil(info->sink / T) + std::ceil(info->window / T) + 1.0;
+    if (info->max_item_tiles < 1.5 * streaming)
+        return (int32_t)n;
+    const LaunchCost c = tile_cost(nw);
+    const double tps = info->tile / (double)kStep;
+    const double mean = tps * (double)info->kept_tiles_per_qhead / (double)n;
+    const double all = (double)wgs / c.slots * c.wg(mean);
+    const double left = c.wg(tps * info->max_item_tiles) + 0.5 * c.wg(mean);
+    if (left < (nw <= 4 ? 0.3 : 0.15) * all)
+        return (int32_t)n;
+    const double span = (double)n * std::max(0.0, 1.0 - left / all);
+    return (int32_t)std::min((double)n, std::max((double)nl, span));
 }
 
 template <int D>
@@ -2394,8 +2454,8 @@ int units_per_wg(const FwdArgs &a, int kind, int nw, int64_t units, int32_t max_
     }
 }
 
-ta_status launch_tiles(int kind, const FwdArgs &a_in, int32_t head_dim, int32_t max_item_tiles,
-                       hipStream_t stream)
+ta_status launch_tiles(int kind, const FwdArgs &a_in, int32_t head_dim,
+                       const ta_schedule_info *info, hipStream_t stream)
 {
     if (a_in.n_items <= 0)
         return TA_OK;
@@ -2405,7 +2465,7 @@ ta_status launch_tiles(int kind, const FwdArgs &a_in, int32_t head_dim, int32_t 
     hipError_t err;
     // Triangle passes over workgroups of five to eight waves run several
     // units per workgroup (multi-unit kernel); the others one.
-    const int upw = units_per_wg(a, kind, nw, units, max_item_tiles, head_dim);
+    const int upw = units_per_wg(a, kind, nw, units, info->max_item_tiles, head_dim);
     if (upw > 1) {
         a.n_units = (int32_t)units;
         a.upw = upw;
@@ -2414,6 +2474,8 @@ ta_status launch_tiles(int kind, const FwdArgs &a_in, int32_t head_dim, int32_t 
         err = head_dim == 128 ? launch_units<128>(nw, grid, a, kind, stream)
                               : launch_units<64>(nw, grid, a, kind, stream);
     } else {
+        a.lead_span = lead_slots(a, info, nw, units * a.hkv);
+        a.n_lead = a.lead_span > 0 ? info->n_last_items : 0;
         dim3 grid((unsigned)(units * a.hkv));
         err = head_dim == 128 ? launch_tile<128>(nw, grid, a, kind, stream)
                               : launch_tile<64>(nw, grid, a, kind, stream);
@@ -2509,7 +2571,7 @@ extern "C" ta_status triangle_attn_tiles(const void *q, const void *k, const voi
         return st;
     const FwdArgs a = make_args(q, k, v, o, o_dtype, lse, sched_dev, info, total_tokens,
                                 hq, hkv, softmax_scale, part_o, part_lse);
-    return launch_tiles(TA_KIND_TRIANGLE, a, head_dim, info->max_item_tiles,
+    return launch_tiles(TA_KIND_TRIANGLE, a, head_dim, info,
                         static_cast<hipStream_t>(stream));
 }
 
@@ -2573,7 +2635,7 @@ ta_status split_pass_fwd(const char *fn, int kind, const void *q, const void *k,
     const hipStream_t s = static_cast<hipStream_t>(stream);
     const FwdArgs a = make_args(q, k, v, o, o_dtype, lse, sched_dev, info, total_tokens,
                                 hq, hkv, softmax_scale, part_o, part_lse);
-    st = launch_tiles(kind, a, head_dim, info->max_item_tiles, s);
+    st = launch_tiles(kind, a, head_dim, info, s);
     if (st != TA_OK)
         return st;
     return launch_merge(o, o_dtype, lse, sched_dev, info, total_tokens, hq, head_dim,
@@ -2696,6 +2758,6 @@ extern "C" ta_status causal_attn_fwd(const void *q, const void *k, const void *v
         return st;
     const FwdArgs a = make_args(q, k, v, o, o_dtype, lse, sched_dev, info, total_tokens,
                                 hq, hkv, softmax_scale, nullptr, nullptr);
-    return launch_tiles(TA_KIND_CAUSAL, a, head_dim, info->max_item_tiles,
+    return launch_tiles(TA_KIND_CAUSAL, a, head_dim, info,
                         static_cast<hipStream_t>(stream));
 }

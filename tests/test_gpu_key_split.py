@@ -1,0 +1,91 @@
+"""GPU tests of the key-split form of the tile kernel: the two ping-pong
+groups of a workgroup own the same four row blocks and take the 64-key steps
+in turn, and their partial results are combined through LDS.
+
+The launches here are small, so the library chooses that form by its own
+rule; with TRIATTN_UNITS_PER_WG=1 the same call runs the plain form.  Sizes
+sit where the form can go wrong: one step, an odd number of steps (the last
+step of the second group then holds no kept key), row blocks of several heads
+with a remainder in the last workgroup, tiles of 64 rows whose workgroups are
+not full, ragged last tiles, tiles past the end of the sequence, list items,
+split items, both head dimensions and both output types."""
+import math
+import os
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2507_21526_amd import binding
+from paper_2507_21526_amd.inputs import draw_qkv
+from tests.parity import compare, log, run_pass
+
+pytestmark = pytest.mark.gpu
+
+ENV = "TRIATTN_UNITS_PER_WG"
+
+CASES = [
+    # kind, cu, hq, hkv, d, S, W, L, T, splits
+    ("causal", [0, 33], 1, 1, 128, 0, 1, 0, 128, 0),              # one step, one row block
+    ("causal", [0, 65], 4, 1, 64, 0, 1, 0, 64, 0),                # second step of one key
+    ("causal", [0, 191, 192, 449], 5, 1, 128, 0, 1, 0, 128, 0),   # G 5: 20 row blocks
+    ("causal", [0, 700], 6, 2, 64, 0, 1, 0, 64, 0),               # G 3, T 64: six blocks
+    ("causal", [0, 1000], 7, 1, 128, 0, 1, 0, 64, 0),             # G 7, T 64: 14 blocks
+    ("triangle", [0, 1537], 8, 8, 128, 8, 130, 40, 128, 0),       # G 1: 128 rows of a head
+    ("triangle", [0, 64, 900], 4, 2, 64, 130, 65, 129, 128, 3),   # sink not aligned, splits
+    ("triangle", [0, 1000], 8, 1, 128, 16, 1, 200, 128, 8),       # splits without steps
+    ("triangle", [0, 2000], 6, 1, 128, 0, 320, 0, 128, 0),        # no Last rows, no sink
+]
+
+
+def _run(plain, *args, **kw):
+    if plain:
+        os.environ[ENV] = "1"
+    try:
+        o, lse, _ = run_pass(*args, poison=True, **kw)
+        torch.cuda.synchronize()
+    finally:
+        os.environ.pop(ENV, None)
+    return o, lse
+
+
+@pytest.mark.parametrize("kind,cu,hq,hkv,d,S,W,L,T,splits", CASES)
+def test_key_split(kind, cu, hq, hkv, d, S, W, L, T, splits):
+    log(f"case key split {kind} cu={cu} hq={hq} hkv={hkv} d={d} S={S} W={W} L={L} T={T}")
+    q, k, v = draw_qkv(cu, hq, hkv, d, seed=31 + hq + S)
+    args = [kind] + [t.cuda() for t in (q, k, v)] + [cu, S, W, L, T, splits]
+    for plain in (False, True):
+        o, lse = _run(plain, *args)
+        assert not torch.isnan(o).any() and not torch.isnan(lse).any()
+        compare(kind, q, k, v, cu, S, W, L, 1 / math.sqrt(d), o, lse, np.arange(cu[-1]),
+                range(hq), label=f"{kind} plain={plain} cu={cu}", p_bound=True)
+        if cu[-1] > 64:  # the forms differ in rounding, so in some value
+            seen = o if not plain else torch.equal(seen, o)
+    assert cu[-1] <= 64 or seen is False
+    o, _ = _run(False, *args)
+    o16, _ = _run(False, *args, out_dtype=torch.bfloat16)
+    assert torch.equal(o16, o.bfloat16())
+
+
+@pytest.mark.parametrize("hq,d,T,bound", [(5, 128, 128, 0), (3, 64, 64, 3)])
+def test_key_split_lists_equal_causal(hq, d, T, bound):
+    """Full lists, an odd number of tiles among them: uncut they give the
+    causal pass's rows bit for bit; cut into items of three tiles they meet the
+    parity bar."""
+    cu = [0, 450, 1100]
+    q, k, v = draw_qkv(cu, hq, 1, d, seed=77)
+    qg, kg, vg = (t.cuda() for t in (q, k, v))
+    ptr, idx = [0], []
+    for n in np.diff(cu):
+        for t in range(-(-int(n) // T)):
+            idx += range(t + 1)
+            ptr.append(len(idx))
+    plan = binding.Plan("blocksparse", cu, 0, 1, 0, T, hq, d, splits=bound, blocks=(ptr, idx))
+    o = torch.full((cu[-1], hq, d), math.nan, device="cuda")
+    lse = torch.full((hq, cu[-1]), math.nan, device="cuda")
+    plan.run(qg, kg, vg, o, lse)
+    ref, ref_lse = _run(False, "causal", qg, kg, vg, cu, 0, 1, 0, T, 0)
+    if bound == 0:
+        assert torch.equal(o, ref) and torch.equal(lse, ref_lse)
+    compare("causal", q, k, v, cu, 0, 1, 0, 1 / math.sqrt(d), o, lse, np.arange(cu[-1]),
+            range(hq), label=f"lists hq={hq} d={d} T={T}", p_bound=True)

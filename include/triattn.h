@@ -233,7 +233,9 @@ ta_status triangle_attn_fwd_noalloc(const void *q, const void *k, const void *v,
 
 /*
  * The two passes of triangle_attn_fwd, callable on their own (same stream
- * order: tiles, then merge); triangle_attn_fwd is exactly these two calls.
+ * order: tiles, then merge); triangle_attn_fwd gives what these two calls
+ * give (where every Last q-tile has one split it writes the Last rows in the
+ * first pass and needs no second).
  *
  * triangle_attn_tiles: the attention pass over every schedule item (Appendix
  *   A.1: streaming q-tiles over their sink and window k-tiles; Last q-tiles

@@ -91,7 +91,18 @@ struct FwdArgs {
     int32_t n_lead;
     int32_t lead_span;
     int32_t key_split;    // the key-split form of the tile kernel
+    // every Last q-tile has one split, which covers its keys: its rows go
+    // straight to O and LSE, and no merge follows
+    int32_t direct;
 };
+
+// Whether a Last split item of a direct pass is what that pass needs: all
+// keys of its rows in one run.
+__device__ __forceinline__ bool covers_rows(int mode, int ka0, int ka1, int kb0, int kb1, int r1,
+                                            int tile)
+{
+    return (mode == kModeCausal) & (ka0 == 0) & ((int64_t)ka1 * tile >= r1) & (kb0 == kb1);
+}
 
 struct MergeArgs {
     const int32_t *sched;
@@ -384,7 +395,7 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void attn_tile_kernel(Fwd
     const int32_t ka0 = it[I_KA0], ka1 = it[I_KA1];
     const int32_t kb0 = it[I_KB0], kb1 = it[I_KB1];
     const int32_t mode = it[I_MODE];
-    const int32_t part_base = it[I_PART_BASE];
+    const int32_t item_part = it[I_PART_BASE];
     // Guard against a schedule that does not match the launch, and against a
     // malformed item: never touch memory outside it; poison the outputs.
     // Block-sparse schedules record the length of their k-tile lists.  List
@@ -395,6 +406,7 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void attn_tile_kernel(Fwd
     // One combined test without short-circuits: the header and item words
     // are all loaded before it.
     const int32_t list_len = sched[H_WINDOW];  // block-sparse: length of the lists
+    const bool uncovered = !covers_rows(mode, ka0, ka1, kb0, kb1, r1, a.tile);
     const bool bad =
         !header_ok(sched, a.total_tokens, a.n_items, kind) |
         (a.list_words != (kind == TA_KIND_BLOCKSPARSE ? list_len : 0)) |
@@ -403,14 +415,16 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void attn_tile_kernel(Fwd
         (mode != kModeStreaming && mode != kModeCausal && !list_mode) |
         (list_mode ? (ka1 < 0) | (kb1 != kb0) | ((int64_t)ka0 + ka1 > a.list_words)
                    : ka1 < ka0) |
-        ((part_base >= 0) & (part_base + (r1 - r0) > a.n_partial_rows));
+        ((item_part >= 0) & ((item_part + (r1 - r0) > a.n_partial_rows) |
+                             ((a.direct != 0) & uncovered)));
     if (bad) {
         poison_outputs(a.o, a.o_f32, a.lse, a.total_tokens, a.hq, D, blockIdx.x,
                        gridDim.x);
         poison_item_rows(a.o, a.o_f32, a.lse, a.part_o, a.part_lse, a.total_tokens, a.hq, D,
-                         a.n_partial_rows, a.tile, seq_off, r0, r1, part_base);
+                         a.n_partial_rows, a.tile, seq_off, r0, r1, item_part);
         return;
     }
+    const int32_t part_base = a.direct ? -1 : item_part;
     const int32_t *tile_list = sched + a.list_base + (list_mode ? ka0 : 0);
     const int max_ktile = seq_len > 0 ? (seq_len - 1) / a.tile : 0;
 
@@ -1808,17 +1822,20 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_units_kernel(FwdArgs a, int32
         const int kb0 = __builtin_amdgcn_readfirstlane(w[I_KB0]);
         const int kb1 = __builtin_amdgcn_readfirstlane(w[I_KB1]);
         const int mode = __builtin_amdgcn_readfirstlane(w[I_MODE]);
-        const int part_base = __builtin_amdgcn_readfirstlane(w[I_PART_BASE]);
+        const int item_part = __builtin_amdgcn_readfirstlane(w[I_PART_BASE]);
         if (seq_off < 0 || seq_len < 0 || (int64_t)seq_off + seq_len > a.total_tokens ||
             r0 < 0 || r1 > seq_len || r0 >= r1 || ka0 < 0 || ka1 < ka0 || kb0 < 0 ||
             kb1 < kb0 || (mode != kModeStreaming && mode != kModeCausal) ||
-            (part_base >= 0 && part_base + (r1 - r0) > a.n_partial_rows)) {
+            (item_part >= 0 &&
+             (item_part + (r1 - r0) > a.n_partial_rows ||
+              (a.direct && !covers_rows(mode, ka0, ka1, kb0, kb1, r1, a.tile))))) {
             poison_outputs(a.o, a.o_f32, a.lse, a.total_tokens, a.hq, D, blockIdx.x,
                            gridDim.x);
             poison_item_rows(a.o, a.o_f32, a.lse, a.part_o, a.part_lse, a.total_tokens, a.hq,
-                             D, a.n_partial_rows, a.tile, seq_off, r0, r1, part_base);
+                             D, a.n_partial_rows, a.tile, seq_off, r0, r1, item_part);
             return;
         }
+        const int part_base = a.direct ? -1 : item_part;
         const int sub = (slot + k * a.n_slots) % a.subtiles;
         const int wr0 = r0 + sub * a.rows_per_wg;
         if (wr0 >= r1)
@@ -2613,6 +2630,7 @@ FwdArgs make_args(const void *q, const void *k, const void *v, void *o,
     a.n_slots = 0;
     a.upw = 1;
     a.key_split = 0;
+    a.direct = 0;
     a.n_lead = 0;
     a.lead_span = 0;
     return a;
@@ -2971,10 +2989,18 @@ ta_status split_pass_fwd(const char *fn, int kind, const void *q, const void *k,
     if (st != TA_OK)
         return st;
     const hipStream_t s = static_cast<hipStream_t>(stream);
-    const FwdArgs a = make_args(q, k, v, o, o_dtype, lse, sched_dev, info, total_tokens,
-                                hq, hkv, softmax_scale, part_o, part_lse);
+    FwdArgs a = make_args(q, k, v, o, o_dtype, lse, sched_dev, info, total_tokens, hq, hkv,
+                          softmax_scale, part_o, part_lse);
+    // Last q-tiles of one split each (sequences of up to 2048 keys or one
+    // streaming item's worth, or an explicit split count of 1): a merge would
+    // copy the one partial, weight exp(0) = 1, so the tile pass writes the
+    // rows itself, with the same values, and the merge launch (4 us at 1024
+    // tokens, 4 to 10 us for a few short sequences) and the partials' trip
+    // through memory fall away.
+    a.direct = kind == TA_KIND_TRIANGLE && info->max_splits == 1 &&
+               info->n_last_items == info->n_merge_items;
     st = launch_tiles(kind, a, head_dim, info, s);
-    if (st != TA_OK)
+    if (st != TA_OK || a.direct)
         return st;
     return launch_merge(o, o_dtype, lse, sched_dev, info, total_tokens, hq, head_dim,
                         part_o, part_lse, s);

@@ -89,3 +89,39 @@ def test_key_split_lists_equal_causal(hq, d, T, bound):
         assert torch.equal(o, ref) and torch.equal(lse, ref_lse)
     compare("causal", q, k, v, cu, 0, 1, 0, 1 / math.sqrt(d), o, lse, np.arange(cu[-1]),
             range(hq), label=f"lists hq={hq} d={d} T={T}", p_bound=True)
+
+
+@pytest.mark.parametrize("upw", [None, 1, 3])
+@pytest.mark.parametrize("cu,hq,d,T,splits", [
+    ([0, 513], 4, 128, 128, 0),            # the second Last q-tile has one row
+    ([0, 0, 40, 900, 901], 8, 64, 64, 0),  # sequences shorter than L
+    ([0, 5000], 2, 128, 128, 1),           # one split by request
+])
+def test_one_split_needs_no_merge(cu, hq, d, T, splits, upw):
+    """Where every Last q-tile has one split the fused call writes its rows
+    in the tile pass: bit for bit what tiles and merge give, in every form of
+    the kernel, and a split that does not cover its rows is rejected."""
+    S, W, L = 5, 200, 129
+    q, k, v = (t.cuda() for t in draw_qkv(cu, hq, 1, d, seed=5))
+    if upw is not None:
+        os.environ[ENV] = str(upw)
+    try:
+        plan = binding.Plan("triangle", cu, S, W, L, T, hq, d, splits)
+        assert plan.info.max_splits == 1
+        for dtype in (torch.float32, torch.bfloat16):
+            o = torch.full((cu[-1], hq, d), math.nan, device="cuda", dtype=dtype)
+            lse = torch.full((hq, cu[-1]), math.nan, device="cuda")
+            o2, lse2 = o.clone(), lse.clone()
+            plan.run(q, k, v, o, lse)
+            args = (plan.sched, plan.info)
+            binding.triangle_attn_tiles(q, k, v, o2, lse2, *args, d ** -0.5, plan.workspace)
+            binding.triangle_attn_merge(o2, lse2, *args, plan.workspace)
+            torch.cuda.synchronize()
+            assert not torch.isnan(o).any() and not torch.isnan(lse).any()
+            assert torch.equal(o, o2) and torch.equal(lse, lse2)
+        plan.sched[binding.HDR_WORDS + 4] = 1  # the first split misses k-tile 0
+        plan.run(q, k, v, o, lse)
+        torch.cuda.synchronize()
+        assert torch.isnan(o).any()
+    finally:
+        os.environ.pop(ENV, None)

@@ -335,6 +335,24 @@ ta_status region_grad_probe(const void *q, const void *k, const void *v,
                             size_t workspace_bytes, void *stream);
 
 /*
+ * The same sums without a given LSE: the row normalisers are carried online
+ * beside the sums, so no causal pass has to run first.  Arguments as
+ * region_grad_probe minus lse; workspace of at least
+ * ta_region_grad_workspace_bytes(info, hq, hkv) bytes, 16-byte aligned (NULL
+ * when that is 0), its contents on entry do not matter.  Every causal row
+ * keeps its own key, so no normaliser is 0.  Deterministic; errors as
+ * region_grad_probe.
+ */
+size_t ta_region_grad_workspace_bytes(const ta_schedule_info *info, int32_t hq, int32_t hkv);
+ta_status region_grad_sums(const void *q, const void *k, const void *v,
+                           const void *dout, const int32_t *sched_dev,
+                           const ta_schedule_info *info, int64_t total_tokens,
+                           int32_t hq, int32_t hkv, int32_t head_dim,
+                           float softmax_scale, int32_t sink, int32_t window,
+                           int32_t last, double *region_sums, void *workspace,
+                           size_t workspace_bytes, void *stream);
+
+/*
  * Host helpers of the probe (Appendix A.3 sections; Sec. 3 layer choice).
  * ta_region_counts: pairs (i, j) per head in each section (streaming,
  *   middle, last), summed over the sequences of cu_seqlens[batch + 1]

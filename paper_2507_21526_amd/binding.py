@@ -116,6 +116,12 @@ def lib():
     L.region_grad_probe.argtypes = [vp, vp, vp, vp, vp, vp, pinfo, i64, i32, i32,
                                     i32, ctypes.c_float, i32, i32, i32, vp, vp,
                                     ctypes.c_size_t, vp]
+    L.ta_region_grad_workspace_bytes.restype = ctypes.c_size_t
+    L.ta_region_grad_workspace_bytes.argtypes = [pinfo, i32, i32]
+    L.region_grad_sums.restype = ctypes.c_int
+    L.region_grad_sums.argtypes = [vp, vp, vp, vp, vp, pinfo, i64, i32, i32, i32,
+                                   ctypes.c_float, i32, i32, i32, vp, vp,
+                                   ctypes.c_size_t, vp]
     L.ta_region_counts.restype = ctypes.c_int
     L.ta_region_counts.argtypes = [vp, i32, i32, i32, i32, vp]
     L.ta_region_grad_mean.restype = ctypes.c_int
@@ -394,6 +400,31 @@ def region_grad_probe(q, k, v, dout, lse, sched_dev, info, softmax_scale, sink,
         last, _ptr(region_sums), _ptr(workspace), ws_bytes, _stream(stream)))
 
 
+def ta_region_grad_workspace_bytes(info: ScheduleInfo, hq: int, hkv: int) -> int:
+    return int(lib().ta_region_grad_workspace_bytes(ctypes.byref(info), hq, hkv))
+
+
+def region_grad_sums(q, k, v, dout, sched_dev, info, softmax_scale, sink, window, last,
+                     region_sums, workspace, stream=None):
+    """Enqueue the region-contribution sums on ``stream`` without a given LSE.
+
+    Arguments as region_grad_probe minus lse; workspace uint8 cuda tensor of
+    >= ta_region_grad_workspace_bytes bytes or None.
+    """
+    import torch
+    if not isinstance(dout, torch.Tensor) or dout.dtype != torch.bfloat16:
+        raise ValueError(f"dout must be a bfloat16 tensor, got {getattr(dout, 'dtype', dout)}")
+    _check_tensors(q, k, v, dout, None, sched_dev, info, workspace,
+                   extra=(("region_sums", region_sums, torch.float64, (q.shape[1], 3)),))
+    total, hq, d = q.shape
+    hkv = k.shape[1]
+    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
+    _check(lib().region_grad_sums(
+        _ptr(q), _ptr(k), _ptr(v), _ptr(dout), _ptr(sched_dev), ctypes.byref(info), total,
+        hq, hkv, d, float(softmax_scale), sink, window, last, _ptr(region_sums),
+        _ptr(workspace), ws_bytes, _stream(stream)))
+
+
 def ta_region_counts(cu_seqlens, sink, window, last) -> np.ndarray:
     """Pairs per head in the (streaming, middle, last) sections."""
     cu = np.ascontiguousarray(np.asarray(cu_seqlens, dtype=np.int32))
@@ -417,27 +448,26 @@ def ta_region_grad_mean(region_sums, counts) -> np.ndarray:
 def region_grad(q, k, v, dout, cu_seqlens, sink, window, last, tile=128,
                 softmax_scale=None, stream=None):
     """Grad(M-hat, l) of one layer for the (streaming, middle, last)
-    sections, and the per-head sums behind it: the causal pass writes each
-    row's LSE, the probe sums A_ij <dO_i, V_j> per head and section, and the
-    library divides by Hq times the section's pair count.  Returns (grad [3],
-    sums [Hq, 3]) as numpy float64; synchronises the stream to read them."""
+    sections, and the per-head sums behind it: one pass sums A_ij <dO_i, V_j>
+    per head and section, carrying each row's softmax normaliser along, and
+    the library divides by Hq times the section's pair count.  Returns (grad
+    [3], sums [Hq, 3]) as numpy float64; synchronises the stream to read
+    them."""
     import torch
     total, hq, d = q.shape
     if softmax_scale is None:
         softmax_scale = 1.0 / float(d) ** 0.5
     plan = Plan("causal", cu_seqlens, 0, 1, 0, tile, hq, d, device=q.device)
-    o = torch.empty(q.shape, dtype=torch.bfloat16, device=q.device)
-    lse = torch.empty((hq, total), dtype=torch.float32, device=q.device)
-    plan.run(q, k, v, o, lse, softmax_scale, stream)
-    nbytes = ta_probe_workspace_bytes(plan.info, hq)
+    # (a head count that k's does not divide is refused by the call below)
+    nbytes = ta_region_grad_workspace_bytes(plan.info, hq, k.shape[1])
     ws = torch.empty(nbytes, dtype=torch.uint8, device=q.device) if nbytes else None
     sums = torch.empty((hq, 3), dtype=torch.float64, device=q.device)
-    region_grad_probe(q, k, v, dout, lse, plan.sched, plan.info, softmax_scale, sink,
-                      window, last, sums, ws, stream)
+    region_grad_sums(q, k, v, dout, plan.sched, plan.info, softmax_scale, sink, window,
+                     last, sums, ws, stream)
+    counts = ta_region_counts(cu_seqlens, sink, window, last)
     (stream or torch.cuda.current_stream()).synchronize()
     sums_host = sums.cpu().numpy()
-    return ta_region_grad_mean(sums_host, ta_region_counts(cu_seqlens, sink, window, last)), \
-        sums_host
+    return ta_region_grad_mean(sums_host, counts), sums_host
 
 
 def ta_select_triangle_layers(grad_middle, n_triangle) -> list:

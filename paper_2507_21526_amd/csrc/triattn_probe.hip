@@ -31,6 +31,17 @@
 // the partials of each (head, section) in a fixed order, so results are
 // deterministic.  Roofline: MFMA, 4 T^2 d flops per kept (q-tile, k-tile)
 // pair and head, as the forward pass.
+//
+// Online form (region_grad_sums): no LSE is given, and none is computed by a
+// pass of its own; the kernel keeps the online softmax state of each row (a
+// lazily re-based maximum m and l = sum_j 2^(S_j c - m)) beside the row's two
+// unnormalised section sums, and divides them by l at the end.  A causal pass
+// for the LSE alone would do a second Q K^T, a P V product nobody reads and
+// write O: at 2K tokens (32 heads over 8) it takes as long as the probe
+// itself (49 beside 44 us), against the few vector operations per score that
+// the row state costs here, which hide behind the matrix phase.  Where a
+// row's keys are spread over several workgroups each writes the row's (m, l,
+// sums) for its chunk and probe_combine_kernel merges them.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -76,7 +87,16 @@ struct ProbeArgs {
     int32_t n_slots;      // workgroups per (kv head, row block)
     int32_t per_item;     // 1: workgroup slot runs item slot whole
     int64_t total_cost;   // kept k-tiles per head (the items' costs summed)
+    // online form over equal shares: row states of chunk slot + item (a share
+    // or an item ends with every chunk, so no two chunks of a row block have
+    // the same index), [chunk, head, row of the q-tile]
+    double2 *row_sums;    // unnormalised section sums: streaming, other
+    float2 *row_ml;       // m and l
 };
+
+// A re-based probability stays at most 2^8: the bound on a step's sum that
+// lets it go without a new row maximum.
+constexpr float kProbeRescaleBound = 256.0f;
 
 // 16-byte chunk swizzle of LDS row r: the 32 rows one operand fetch reads
 // land on distinct banks.
@@ -97,7 +117,7 @@ __device__ __forceinline__ bool probe_header_ok(const int32_t *s, int64_t total,
            (s[H_ITEMS] == n_items) & (s[H_KEPT_TILES] == kept);
 }
 
-template <int D, int NW>
+template <int D, int NW, bool ONLINE>
 __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void probe_kernel(ProbeArgs a)
 {
     constexpr int ROW_BYTES = 2 * D;
@@ -349,17 +369,32 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void probe_kernel(ProbeAr
         const int key_end = min(ka0 * a.tile + s1 * kProbeStep, wg_last + 1);
         const int nsteps =
             key_end > key_begin ? (key_end - key_begin + kProbeStep - 1) / kProbeStep : 0;
-        if (nsteps == 0)
-            continue;  // the share holds no keys of these rows (uniform)
-
         const int row_base = wr0 + (wave % wph) * 32;
         const int my_row = row_base + r_lane;
         const bool row_valid = my_row < r1;
+        // the row's state for this chunk, for the combine kernel
+        auto put_row = [&](float m, float l, double us, double uo) TA_INLINE {
+            if (row_valid && h == 0) {
+                const int64_t at =
+                    ((int64_t)(slot + item) * a.hq + head) * a.tile + (my_row - r0);
+                a.row_ml[at] = float2{m, l};
+                a.row_sums[at] = double2{us, uo};
+            }
+        };
+        if (nsteps == 0) {
+            // the share holds no keys of these rows (uniform)
+            if constexpr (ONLINE)
+                if (!a.per_item)
+                    put_row(-INFINITY, 0.f, 0.0, 0.0);
+            continue;
+        }
+
         const int load_row = row_valid ? my_row : r1 - 1;
         const int row_hi = min(row_base + 31, r1 - 1);  // last valid row of the wave
         const bool last_row = my_row >= seq_len - min(a.last, seq_len);
-        const float lse2 = a.lse[(int64_t)head * a.total_tokens + seq_off + load_row] *
-                           kProbeLog2e;
+        float lse2 = 0.f;
+        if constexpr (!ONLINE)
+            lse2 = a.lse[(int64_t)head * a.total_tokens + seq_off + load_row] * kProbeLog2e;
 
         // B operands: lane holds Q[row][16 s + 8 h ..] and dO[row][16 s + 8 h ..]
         bf16x8 qf[QK], df[QK];
@@ -391,7 +426,9 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void probe_kernel(ProbeAr
         // The first KPRE operand fragments of a matrix phase (its first MFMAs'
         // K and V reads, in MFMA order) can be read ahead in the wave's vector
         // phase before it, when the stage has landed by then (group 1).
-        constexpr int KPRE = 6;
+        // (two only in the online form at two workgroups per CU, whose row state
+        // leaves no registers for six)
+        constexpr int KPRE = ONLINE && NW == 4 ? 2 : 6;
         bf16x8 kpre[KPRE];
         auto frag = [&](const uint8_t *kt, int i) TA_INLINE -> bf16x8 {
             // read i of a matrix phase: s = i / 4; k0, v0, k1, v1
@@ -469,7 +506,101 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void probe_kernel(ProbeAr
         // edge classify each pair.  Rows past the q-tile are dropped when the
         // chunk ends.
         double chunk_s = 0.0, chunk_o = 0.0;  // streaming / other (middle or last)
+        // online form: reference maximum (log2 domain) and row sum
+        float m_ref = -INFINITY;
+        double chunk_l = 0.0;
+        bool fresh = true;
+        // Vector phase of the online form: the probabilities are taken
+        // against the kept reference; only when their sum passes the bound
+        // (or no reference is set) does the wave find the row maxima, re-base
+        // to them and redo the step.  Masked scores are -inf, so p = 0, and
+        // their products are dropped by the same test, so that a dP of a
+        // masked key does not matter whatever it is.
+        auto do_x_online = [&](int j) TA_INLINE {
+            const int key0 = key_begin + j * kProbeStep;
+            const int lim = my_row - key0 - 4 * h;  // causal: o <= lim
+            const bool causal_all = key0 + kProbeStep - 1 <= row_base;
+            const bool strm_all = key0 + kProbeStep - 1 < a.sink || row_hi - key0 < a.window;
+            const bool strm_none =
+                key0 >= a.sink && row_base - (key0 + kProbeStep - 1) >= a.window;
+            const bool one_section = strm_all || strm_none;
+            auto at = [](int kb, int e) { return 32 * kb + (e & 3) + 8 * (e >> 2); };
+            if (!causal_all) {
+#pragma unroll
+                for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e)
+                        sacc[kb][e] = at(kb, e) <= lim ? sacc[kb][e] : -INFINITY;
+            }
+            float ts = 0.f, to = 0.f;
+            auto pass = [&](float m) TA_INLINE -> float {
+                float psum = 0.f, t = 0.f;
+                if (one_section && causal_all) {
+#pragma unroll
+                    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                        for (int e = 0; e < 16; ++e) {
+                            const float pr = __builtin_amdgcn_exp2f(fmaf(sacc[kb][e], c, -m));
+                            psum += pr;
+                            t = fmaf(pr, gacc[kb][e], t);
+                        }
+                    ts = strm_all ? t : 0.f;
+                    to = strm_all ? 0.f : t;
+                } else {
+                    // sink key: o < slim; in the window: o > wlim
+                    const int slim = strm_all ? kProbeStep : a.sink - key0 - 4 * h;
+                    const int wlim = strm_none ? kProbeStep : lim - a.window;
+                    float st = 0.f;
+#pragma unroll
+                    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                        for (int e = 0; e < 16; ++e) {
+                            const int o = at(kb, e);
+                            const float pr = __builtin_amdgcn_exp2f(fmaf(sacc[kb][e], c, -m));
+                            const float pv = o <= lim ? pr * gacc[kb][e] : 0.f;
+                            psum += pr;
+                            t += pv;
+                            st += ((o < slim) | (o > wlim)) ? pv : 0.f;
+                        }
+                    ts = st;
+                    to = t - st;
+                }
+                return psum;
+            };
+            float psum = INFINITY;
+            if (!fresh)
+                psum = pass(m_ref);
+            fresh = false;
+            if (__builtin_amdgcn_ballot_w64(!(psum <= kProbeRescaleBound)) != 0) {
+                float mx = -INFINITY;
+#pragma unroll
+                for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e)
+                        mx = fmaxf(mx, sacc[kb][e]);
+                mx = fmaxf(mx, __shfl_xor(mx, 32));
+                const float m_new = fmaxf(m_ref, mx * c);
+                const float m_use = m_new == -INFINITY ? 0.f : m_new;
+                const double alpha = (double)__builtin_amdgcn_exp2f(m_ref - m_use);
+                chunk_l *= alpha;
+                chunk_s *= alpha;
+                chunk_o *= alpha;
+                m_ref = m_new;
+                psum = pass(m_use);
+            }
+            chunk_l += (double)psum;
+            chunk_s += (double)ts;
+            chunk_o += (double)to;
+            fence_regs(chunk_l);
+            fence_regs(chunk_s);
+            fence_regs(chunk_o);
+            fence_regs(m_ref);
+        };
         auto do_x = [&](int j) TA_INLINE {
+            if constexpr (ONLINE) {
+                do_x_online(j);
+                return;
+            }
             const int key0 = key_begin + j * kProbeStep;
             const int lim = my_row - key0 - 4 * h;  // causal: o <= lim
             const bool causal_all = key0 + kProbeStep - 1 <= row_base;
@@ -601,6 +732,19 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void probe_kernel(ProbeAr
                 end_phase(false);
             }
         }
+        if constexpr (ONLINE) {
+            // the lane pair of a row holds its keys' halves
+            const double l_row = chunk_l + __shfl_xor(chunk_l, 32);
+            const double us = chunk_s + __shfl_xor(chunk_s, 32);
+            const double uo = chunk_o + __shfl_xor(chunk_o, 32);
+            if (!a.per_item) {
+                put_row(m_ref, (float)l_row, us, uo);
+                continue;
+            }
+            // the item holds all keys of its rows
+            chunk_s = h == 0 ? us / l_row : 0.0;
+            chunk_o = h == 0 ? uo / l_row : 0.0;
+        }
         if (row_valid) {
             acc_s += chunk_s;
             if (last_row)
@@ -627,6 +771,81 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void probe_kernel(ProbeAr
         pp[1] = ok ? acc_m : bad;
         pp[2] = ok ? acc_l : bad;
     }
+}
+
+// Online form over equal shares: section sums of one item (q-tile) and head,
+// from the row states its chunks left.  Thread r merges row r over the
+// chunks: the slots whose shares hold steps of the item, found as the probe
+// kernel finds them (item i's virtual range starts at the sum of the costs
+// before it).  Writes one partial per (item, head, section).  Indices stay in
+// the workspace whatever the schedule holds; a malformed one has given NaN
+// partials in the probe kernel already.
+__global__ __launch_bounds__(128) void probe_combine_kernel(ProbeArgs a, double *part)
+{
+    const int item = blockIdx.x, head = blockIdx.y, tid = threadIdx.x, nt = blockDim.x;
+    const int lane = tid & 63, wave = tid >> 6;
+    __shared__ int64_t pre_w[2];
+    __shared__ double sum_w[2][3];
+    const int spt = a.tile / kProbeStep;
+    auto cost_of = [&](int i) -> int64_t {
+        return (int64_t)spt * a.sched[kHdrWords + (int64_t)i * kItemWords + I_COST] +
+               kProbeItemChange;
+    };
+    int64_t x = 0;
+    for (int i = tid; i < item; i += nt)
+        x += cost_of(i);
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1)
+        x += __shfl_xor(x, o);
+    if (lane == 0)
+        pre_w[wave] = x;
+    __syncthreads();
+    const int64_t pre = pre_w[0] + (nt > 64 ? pre_w[1] : 0);
+    const int64_t vtotal = (int64_t)spt * a.total_cost + (int64_t)kProbeItemChange * a.n_items;
+    const int64_t per = (vtotal + a.n_slots - 1) / a.n_slots;
+    const int64_t top = a.n_slots - 1;
+    const int s0 = (int)max<int64_t>(0, min((pre + kProbeItemChange) / per, top));
+    const int s1 = (int)max<int64_t>(0, min((pre + cost_of(item) - 1) / per, top));
+    const int32_t *it = a.sched + kHdrWords + (int64_t)item * kItemWords;
+    const int32_t seq_len = it[I_SEQ_LEN], r0 = it[I_R0], r1 = it[I_R1];
+    double ss = 0.0, sm = 0.0, sl = 0.0;
+    if (tid < a.tile && r0 + tid < r1) {
+        auto at = [&](int s) -> int64_t {
+            return ((int64_t)(s + item) * a.hq + head) * a.tile + tid;
+        };
+        float m = -INFINITY;
+        for (int s = s0; s <= s1; ++s)
+            m = fmaxf(m, a.row_ml[at(s)].x);
+        double l = 0.0, us = 0.0, uo = 0.0;
+        for (int s = s0; s <= s1; ++s) {
+            const float2 ml = a.row_ml[at(s)];
+            const double2 u = a.row_sums[at(s)];
+            // an empty chunk has m = -inf, l = 0 and weight 0
+            const double w = ml.y > 0.f ? exp2((double)ml.x - (double)m) : 0.0;
+            l += w * (double)ml.y;
+            us += w * u.x;
+            uo += w * u.y;
+        }
+        // a row keeps at least its own key, so l > 0 (NaN goes through)
+        ss = us / l;
+        const bool last_row = r0 + tid >= seq_len - min(a.last, seq_len);
+        (last_row ? sl : sm) = uo / l;
+    }
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) {
+        ss += __shfl_xor(ss, o);
+        sm += __shfl_xor(sm, o);
+        sl += __shfl_xor(sl, o);
+    }
+    if (lane == 0) {
+        sum_w[wave][0] = ss;
+        sum_w[wave][1] = sm;
+        sum_w[wave][2] = sl;
+    }
+    __syncthreads();
+    if (tid < 3)
+        part[((int64_t)item * a.hq + head) * 3 + tid] =
+            sum_w[0][tid] + (nt > 64 ? sum_w[1][tid] : 0.0);
 }
 
 // out[hr] = sum over blocks b of part[b, hr] (hr = head * 3 + section), in a
@@ -687,19 +906,55 @@ ProbeSplit probe_split(int nw, int64_t wgs_per_slot, const ta_schedule_info *inf
     return {slots, false};
 }
 
-template <int D>
-hipError_t launch_probe(int nw, dim3 grid, const ProbeArgs &a, hipStream_t s)
+template <int D, bool ONLINE>
+hipError_t launch_probe_as(int nw, dim3 grid, const ProbeArgs &a, hipStream_t s)
 {
     switch (nw) {
-    case 2: hipLaunchKernelGGL((probe_kernel<D, 2>), grid, dim3(128), 0, s, a); break;
-    case 4: hipLaunchKernelGGL((probe_kernel<D, 4>), grid, dim3(256), 0, s, a); break;
-    case 5: hipLaunchKernelGGL((probe_kernel<D, 5>), grid, dim3(320), 0, s, a); break;
-    case 6: hipLaunchKernelGGL((probe_kernel<D, 6>), grid, dim3(384), 0, s, a); break;
-    case 7: hipLaunchKernelGGL((probe_kernel<D, 7>), grid, dim3(448), 0, s, a); break;
-    case 8: hipLaunchKernelGGL((probe_kernel<D, 8>), grid, dim3(512), 0, s, a); break;
+    case 2: hipLaunchKernelGGL((probe_kernel<D, 2, ONLINE>), grid, dim3(128), 0, s, a); break;
+    case 4: hipLaunchKernelGGL((probe_kernel<D, 4, ONLINE>), grid, dim3(256), 0, s, a); break;
+    case 5: hipLaunchKernelGGL((probe_kernel<D, 5, ONLINE>), grid, dim3(320), 0, s, a); break;
+    case 6: hipLaunchKernelGGL((probe_kernel<D, 6, ONLINE>), grid, dim3(384), 0, s, a); break;
+    case 7: hipLaunchKernelGGL((probe_kernel<D, 7, ONLINE>), grid, dim3(448), 0, s, a); break;
+    case 8: hipLaunchKernelGGL((probe_kernel<D, 8, ONLINE>), grid, dim3(512), 0, s, a); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
+}
+
+template <int D>
+hipError_t launch_probe(bool online, int nw, dim3 grid, const ProbeArgs &a, hipStream_t s)
+{
+    return online ? launch_probe_as<D, true>(nw, grid, a, s)
+                  : launch_probe_as<D, false>(nw, grid, a, s);
+}
+
+// The launch shape of a probe over `info`, and the online form's workspace:
+// the fp64 partials of the probe kernel (slot, 32-row block, head, section),
+// those of the combine kernel (item, head, section), then the row states.
+struct ProbeLayout {
+    ProbeSplit split;
+    int64_t subtiles;
+    int nw;
+    int64_t probe_blocks, item_blocks;     // partials per (head, section)
+    size_t sums_at, ml_at, online_bytes;   // byte offsets of the row states
+};
+ProbeLayout probe_layout(const ta_schedule_info *info, int32_t hq, int32_t hkv)
+{
+    ProbeLayout l;
+    const int group = hq / hkv;
+    const int R = probe_rows_per_wg(group, info->tile);
+    l.subtiles = info->tile / R;
+    l.nw = group * R / 32;
+    l.split = probe_split(l.nw, l.subtiles * hkv, info);
+    l.probe_blocks = info->n_items > 0 ? l.split.slots * (info->tile / 32) : 0;
+    l.item_blocks = info->n_items > 0 && !l.split.per_item ? info->n_items : 0;
+    auto aligned = [](size_t n) { return (n + 255) & ~(size_t)255; };
+    const size_t chunks = l.item_blocks > 0 ? (size_t)(l.split.slots + info->n_items) : 0;
+    const size_t rows = chunks * (size_t)hq * (size_t)info->tile;
+    l.sums_at = aligned((size_t)(l.probe_blocks + l.item_blocks) * (size_t)hq * 3 * sizeof(double));
+    l.ml_at = l.sums_at + aligned(rows * sizeof(double2));
+    l.online_bytes = l.ml_at + aligned(rows * sizeof(float2));
+    return l;
 }
 
 }  // namespace
@@ -716,18 +971,17 @@ extern "C" size_t ta_probe_workspace_bytes(const ta_schedule_info *info, int32_t
     return slots * (size_t)(info->tile / 32) * (size_t)hq * 3 * sizeof(double);
 }
 
-extern "C" ta_status region_grad_probe(const void *q, const void *k, const void *v,
-                                       const void *dout, const float *lse,
-                                       const int32_t *sched_dev, const ta_schedule_info *info,
-                                       int64_t total_tokens, int32_t hq, int32_t hkv,
-                                       int32_t head_dim, float softmax_scale, int32_t sink,
-                                       int32_t window, int32_t last, double *region_sums,
-                                       void *workspace, size_t workspace_bytes,
-                                       void *stream_ptr)
+namespace {
+// The two entry points: with the rows' LSE given, or online without it.
+ta_status probe_sums(const char *fn, bool online, const void *q, const void *k, const void *v,
+                     const void *dout, const float *lse, const int32_t *sched_dev,
+                     const ta_schedule_info *info, int64_t total_tokens, int32_t hq, int32_t hkv,
+                     int32_t head_dim, float softmax_scale, int32_t sink, int32_t window,
+                     int32_t last, double *region_sums, void *workspace, size_t workspace_bytes,
+                     void *stream_ptr)
 {
     hipStream_t stream = static_cast<hipStream_t>(stream_ptr);
     clear_error();
-    static const char fn[] = "region_grad_probe";
     if (!info)
         return fail(TA_ERR_INVALID_ARG, "%s: info is NULL", fn);
     if (info->version != TA_SCHEDULE_VERSION)
@@ -764,25 +1018,25 @@ extern "C" ta_status region_grad_probe(const void *q, const void *k, const void 
         return fail(TA_ERR_INVALID_ARG, "%s: region_sums must be a non-NULL 8-byte "
                     "aligned device array", fn);
     if (info->n_items > 0) {
-        if (!q || !k || !v || !dout || !lse || !sched_dev)
+        if (!q || !k || !v || !dout || (!lse && !online) || !sched_dev)
             return fail(TA_ERR_INVALID_ARG, "%s: NULL q, k, v, dout, lse or schedule", fn);
         if (((uintptr_t)q | (uintptr_t)k | (uintptr_t)v | (uintptr_t)dout) & 15)
             return fail(TA_ERR_INVALID_ARG, "%s: q, k, v and dout must be 16-byte aligned", fn);
         if ((uintptr_t)lse & 3)
             return fail(TA_ERR_INVALID_ARG, "%s: lse must be 4-byte aligned", fn);
     }
-    const size_t need = ta_probe_workspace_bytes(info, hq);
-    if (need > 0 && (!workspace || workspace_bytes < need || ((uintptr_t)workspace & 7)))
-        return fail(TA_ERR_WORKSPACE, "%s: workspace needs %zu bytes (8-byte aligned), "
-                    "got %zu", fn, need, workspace_bytes);
-    const int group = hq / hkv;
-    const int R = probe_rows_per_wg(group, info->tile);
-    const int64_t subtiles = info->tile / R;
-    const int nw = group * R / 32;
-    const ProbeSplit split = probe_split(nw, subtiles * hkv, info);
-    const int64_t slots = split.slots;
+    const ProbeLayout lay = probe_layout(info, hq, hkv);
+    const size_t need = !online ? ta_probe_workspace_bytes(info, hq)
+                        : info->n_items > 0 ? lay.online_bytes : 0;
+    const uintptr_t align = online ? 16 : 8;
+    if (need > 0 && (!workspace || workspace_bytes < need || ((uintptr_t)workspace & (align - 1))))
+        return fail(TA_ERR_WORKSPACE, "%s: workspace needs %zu bytes (%d-byte aligned), "
+                    "got %zu", fn, need, (int)align, workspace_bytes);
+    const int64_t subtiles = lay.subtiles, slots = lay.split.slots;
     if (slots * subtiles * hkv > INT32_MAX)
         return fail(TA_ERR_UNSUPPORTED, "%s: grid too large", fn);
+    if (online && 2LL * hq * head_dim >= (1LL << 24))
+        return fail(TA_ERR_UNSUPPORTED, "%s: hq * head_dim too large", fn);
     // per-lane copy offsets use 24-bit multiplies of the K/V row pitch
     if (2LL * hkv * head_dim >= (1LL << 24))
         return fail(TA_ERR_UNSUPPORTED, "%s: hkv * head_dim too large", fn);
@@ -800,26 +1054,42 @@ extern "C" ta_status region_grad_probe(const void *q, const void *k, const void 
         a.total_tokens = total_tokens;
         a.hq = hq;
         a.hkv = hkv;
-        a.group = group;
+        a.group = hq / hkv;
         a.n_items = info->n_items;
         a.tile = info->tile;
-        a.rows_per_wg = R;
+        a.rows_per_wg = info->tile / (int32_t)subtiles;
         a.subtiles = (int32_t)subtiles;
         a.sink = sink;
         a.window = window;
         a.last = last;
         a.scale_log2 = softmax_scale * kProbeLog2e;
         a.n_slots = (int32_t)slots;
-        a.per_item = split.per_item ? 1 : 0;
+        a.per_item = lay.split.per_item ? 1 : 0;
         a.total_cost = info->kept_tiles_per_qhead;
+        a.row_sums = nullptr;
+        a.row_ml = nullptr;
+        if (online) {
+            unsigned char *ws = static_cast<unsigned char *>(workspace);
+            a.row_sums = reinterpret_cast<double2 *>(ws + lay.sums_at);
+            a.row_ml = reinterpret_cast<float2 *>(ws + lay.ml_at);
+        }
         dim3 grid((unsigned)(slots * subtiles * hkv));
-        hipError_t err = head_dim == 128 ? launch_probe<128>(nw, grid, a, stream)
-                                         : launch_probe<64>(nw, grid, a, stream);
+        hipError_t err = head_dim == 128 ? launch_probe<128>(online, lay.nw, grid, a, stream)
+                                         : launch_probe<64>(online, lay.nw, grid, a, stream);
         if (err != hipSuccess)
             return fail(TA_ERR_HIP, "%s: probe kernel launch failed: %s", fn,
                         hipGetErrorString(err));
+        if (online && lay.item_blocks > 0) {
+            hipLaunchKernelGGL(probe_combine_kernel, dim3((unsigned)info->n_items, (unsigned)hq),
+                               dim3((unsigned)info->tile), 0, stream, a,
+                               part + lay.probe_blocks * hq * 3);
+            err = hipGetLastError();
+            if (err != hipSuccess)
+                return fail(TA_ERR_HIP, "%s: combine kernel launch failed: %s", fn,
+                            hipGetErrorString(err));
+        }
     }
-    const int64_t n_blocks = info->n_items > 0 ? slots * (info->tile / 32) : 0;
+    const int64_t n_blocks = lay.probe_blocks + (online ? lay.item_blocks : 0);
     hipLaunchKernelGGL(probe_reduce_kernel, dim3((unsigned)((hq * 3 + 3) / 4)), dim3(256), 0,
                        stream, part, n_blocks, hq * 3, region_sums);
     hipError_t err = hipGetLastError();
@@ -827,6 +1097,42 @@ extern "C" ta_status region_grad_probe(const void *q, const void *k, const void 
         return fail(TA_ERR_HIP, "%s: reduce kernel launch failed: %s", fn,
                     hipGetErrorString(err));
     return TA_OK;
+}
+}  // namespace
+
+extern "C" ta_status region_grad_probe(const void *q, const void *k, const void *v,
+                                       const void *dout, const float *lse,
+                                       const int32_t *sched_dev, const ta_schedule_info *info,
+                                       int64_t total_tokens, int32_t hq, int32_t hkv,
+                                       int32_t head_dim, float softmax_scale, int32_t sink,
+                                       int32_t window, int32_t last, double *region_sums,
+                                       void *workspace, size_t workspace_bytes, void *stream)
+{
+    return probe_sums("region_grad_probe", false, q, k, v, dout, lse, sched_dev, info,
+                      total_tokens, hq, hkv, head_dim, softmax_scale, sink, window, last,
+                      region_sums, workspace, workspace_bytes, stream);
+}
+
+extern "C" size_t ta_region_grad_workspace_bytes(const ta_schedule_info *info, int32_t hq,
+                                                 int32_t hkv)
+{
+    if (!info || hkv <= 0 || hq <= 0 || hq % hkv != 0 || hq / hkv > 8 || info->n_items <= 0 ||
+        (info->tile != 64 && info->tile != 128))
+        return 0;
+    return probe_layout(info, hq, hkv).online_bytes;
+}
+
+extern "C" ta_status region_grad_sums(const void *q, const void *k, const void *v,
+                                      const void *dout, const int32_t *sched_dev,
+                                      const ta_schedule_info *info, int64_t total_tokens,
+                                      int32_t hq, int32_t hkv, int32_t head_dim,
+                                      float softmax_scale, int32_t sink, int32_t window,
+                                      int32_t last, double *region_sums, void *workspace,
+                                      size_t workspace_bytes, void *stream)
+{
+    return probe_sums("region_grad_sums", true, q, k, v, dout, nullptr, sched_dev, info,
+                      total_tokens, hq, hkv, head_dim, softmax_scale, sink, window, last,
+                      region_sums, workspace, workspace_bytes, stream);
 }
 
 extern "C" ta_status ta_region_counts(const int32_t *cu_seqlens, int32_t batch, int32_t sink,

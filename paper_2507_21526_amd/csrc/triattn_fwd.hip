@@ -76,7 +76,8 @@ struct FwdArgs {
     int32_t sink, window;
     int32_t tile;
     int32_t rows_per_wg;  // R
-    int32_t subtiles;     // tile / R
+    int32_t subtiles;     // workgroups per item and kv head
+    int32_t blocks_per_wg;  // row blocks per workgroup where they are dealt out
     int32_t o_f32;
     float scale_log2;     // softmax scale * log2(e)
     // multi-unit kernel: units = items x subtiles per kv head; workgroup
@@ -341,6 +342,14 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void attn_tile_kernel(Fwd
     static_assert(!KS || (NW == 8 && !COPIER), "two groups of four waves");
     constexpr int NC = COPIER ? NW - 1 : NW;  // compute waves
     constexpr int NB = KS ? NW / 2 : NW;      // row blocks (Q tiles)
+    // An item's row blocks (32 rows of one head) are dealt out head first
+    // (block b: head b % G, rows 32 (b / G)..), blocks_per_wg to a workgroup,
+    // by the key-split form and by the eight-wave one, so that eight waves
+    // serve any group: groups of 5 and 6 take three workgroups of a 128-row
+    // tile instead of four of five or six waves (24000 tokens, window 2048:
+    // 1266 to 1003 and 1359 to 1124 us).  The other forms take R rows of
+    // every head.
+    constexpr bool BLOCKS = KS || (NW == 8 && !COPIER);
     constexpr int N_COPY_WAVES = COPIER ? 1 : NW - NW / 2;
     constexpr int COPIES = (N_DMA + N_COPY_WAVES - 1) / N_COPY_WAVES;  // per tile
     constexpr int QK_STEPS = D / 16;
@@ -428,9 +437,8 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void attn_tile_kernel(Fwd
     const int32_t *tile_list = sched + a.list_base + (list_mode ? ka0 : 0);
     const int max_ktile = seq_len > 0 ? (seq_len - 1) / a.tile : 0;
 
-    // First row of this workgroup: row blocks are counted head first (block b
-    // is head b % G, rows 32 (b / G)..) in the key-split form.
-    const int wr0 = KS ? r0 + 32 * (NB * sub / a.group) : r0 + sub * a.rows_per_wg;
+    const int wr0 =  // first row of this workgroup
+        BLOCKS ? r0 + 32 * (a.blocks_per_wg * sub / a.group) : r0 + sub * a.rows_per_wg;
     if (wr0 >= r1)
         return;  // ragged q-tile: nothing for this workgroup
 
@@ -444,8 +452,8 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void attn_tile_kernel(Fwd
     const int col = lane & 31;
     const int block = KS ? wave % NB : wave;  // the wave's Q tile
     int head, row_base;
-    if constexpr (KS) {
-        const int b = NB * sub + block;
+    if constexpr (BLOCKS) {
+        const int b = a.blocks_per_wg * sub + block;
         head = g * a.group + b % a.group;
         row_base = r0 + 32 * (b / a.group);
     } else {
@@ -453,7 +461,7 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void attn_tile_kernel(Fwd
         head = g * a.group + wave / waves_per_head;
         row_base = wr0 + (wave % waves_per_head) * 32;
     }
-    const bool wave_active = row_base < r1;
+    const bool wave_active = row_base < r1 && (!BLOCKS || block < a.blocks_per_wg);
     const int my_row = row_base + col;            // sequence-relative row
     const bool row_valid = my_row < r1;
     const int row_hi = (r1 - 1 < row_base + 31) ? r1 - 1 : row_base + 31;
@@ -464,8 +472,8 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void attn_tile_kernel(Fwd
     // to this workgroup's rows (trim_runs).
     const int tps = a.tile / kStep;
     const int wr_last =
-        (KS ? min(r0 + 32 * ((NB * sub + NB - 1) / a.group + 1), r1)
-            : min(wr0 + a.rows_per_wg, r1)) - 1;
+        (BLOCKS ? min(r0 + 32 * ((a.blocks_per_wg * (sub + 1) - 1) / a.group + 1), r1)
+                : min(wr0 + a.rows_per_wg, r1)) - 1;
     int a_lo = ka0 * tps, a_hi = ka1 * tps, b_lo = kb0 * tps, b_hi = kb1 * tps;
     if (!list_mode)
         trim_runs(mode == kModeStreaming, a.sink, a.window, wr0, wr_last, a_lo, a_hi, b_lo,
@@ -1400,6 +1408,10 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void attn_tile_kernel(Fwd
             } else {
                 run_group0(std::false_type{});
             }
+        } else if (BLOCKS && !wave_active) {
+            // no rows here: the wave keeps the others' barriers
+            for (int p = 0; p < 2 * nsteps + 2; ++p)
+                end_phase(false);
         } else {
             // Group 1's matrix phase M(j) reads stage j & 1, whose K(j) has
             // landed before the phase in which group 1 runs X(j - 1): the
@@ -1538,7 +1550,7 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void attn_tile_kernel(Fwd
     }  // not the key-split form
 }
 
-// Multi-unit form of the tile kernel for workgroups of five to eight waves
+// Multi-unit form of the tile kernel for workgroups of six to eight waves
 // (Q tiles in their own LDS region) over streaming and causal items.  A work
 // unit is one (item, row block) of the schedule for one kv head; workgroup w
 // owns kv head w % hkv and the units slot, slot + n_slots, slot + 2 n_slots,
@@ -2513,8 +2525,6 @@ hipError_t launch_tile_as(int nw, dim3 grid, const FwdArgs &a, int kind, hipStre
     switch (nw) {
     case 2: hipLaunchKernelGGL((attn_tile_kernel<D, 2, false, LIST>), grid, dim3(128), 0, s, a, kind); break;
     case 4: hipLaunchKernelGGL((attn_tile_kernel<D, 4, false, LIST>), grid, dim3(256), 0, s, a, kind); break;
-    case 5: hipLaunchKernelGGL((attn_tile_kernel<D, 5, false, LIST>), grid, dim3(320), 0, s, a, kind); break;
-    case 6: hipLaunchKernelGGL((attn_tile_kernel<D, 6, false, LIST>), grid, dim3(384), 0, s, a, kind); break;
     // seven compute waves and a copier wave
     case 7: hipLaunchKernelGGL((attn_tile_kernel<D, 8, true, LIST>), grid, dim3(512), 0, s, a, kind); break;
     case 8: hipLaunchKernelGGL((attn_tile_kernel<D, 8, false, LIST>), grid, dim3(512), 0, s, a, kind); break;
@@ -2624,6 +2634,7 @@ FwdArgs make_args(const void *q, const void *k, const void *v, void *o,
     a.tile = info->tile;
     a.rows_per_wg = R;
     a.subtiles = info->tile / R;
+    a.blocks_per_wg = 0;
     a.o_f32 = o_dtype == TA_OUT_F32;
     a.scale_log2 = scale * kLog2e;
     a.n_units = 0;
@@ -2652,10 +2663,13 @@ struct LaunchCost {
     }
 };
 // Workgroups of at most four waves run two to a CU, at nearly the speed of
-// one each.
-LaunchCost tile_cost(int nw)
+// one each; one of five row blocks takes its steps a little faster than a
+// full one.
+LaunchCost tile_cost(int nw, int blocks_per_wg)
 {
-    return nw <= 4 ? LaunchCost{10.0, 2.6, 512.0} : LaunchCost{10.0, 2.4, 256.0};
+    if (nw <= 4)
+        return {10.0, 2.6, 512.0};
+    return {10.0, blocks_per_wg == 5 ? 2.25 : 2.4, 256.0};
 }
 
 // The key-split form: a workgroup owns half as many row blocks for half as
@@ -2705,7 +2719,7 @@ bool use_key_split(const FwdArgs &a, const ta_schedule_info *info, int nw, int64
     const PassShape p = pass_shape(info);
     const double rows = p.items * a.hkv;
     return kKeySplitCost.pass(rows * (double)ks_subtiles, p.mean, p.longest) <
-           0.97 * tile_cost(nw).pass(rows * a.subtiles, p.mean, p.longest);
+           0.97 * tile_cost(nw, a.blocks_per_wg).pass(rows * a.subtiles, p.mean, p.longest);
 }
 
 // Launch slots over which a Triangle schedule's Last split items are spread
@@ -2750,7 +2764,6 @@ template <int D>
 hipError_t launch_units(int nw, dim3 grid, const FwdArgs &a, int kind, hipStream_t s)
 {
     switch (nw) {
-    case 5: hipLaunchKernelGGL((attn_units_kernel<D, 5>), grid, dim3(320), 0, s, a, kind); break;
     case 6: hipLaunchKernelGGL((attn_units_kernel<D, 6>), grid, dim3(384), 0, s, a, kind); break;
     case 7: hipLaunchKernelGGL((attn_units_kernel<D, 7>), grid, dim3(448), 0, s, a, kind); break;
     case 8: hipLaunchKernelGGL((attn_units_kernel<D, 8>), grid, dim3(512), 0, s, a, kind); break;
@@ -2766,7 +2779,9 @@ hipError_t launch_units(int nw, dim3 grid, const FwdArgs &a, int kind, hipStream
 // MFMAs), the single-unit kernel reads K ahead where the multi-unit kernel
 // has no registers to, and the pass runs at a power-limited clock, so the
 // multi-unit kernel pays off only for short units, and less at d = 128 than
-// at d = 64: on the paper's sink 8 / window 512 shape (10-12 steps) it is
+// at d = 64 (and not at all for groups of 5 and 6, whose row blocks fill eight
+// waves in the single-unit kernel only: 24000 tokens, sink 64, window 128,
+// group 6: 282 us in units of six waves, 241 without): on the paper's sink 8 / window 512 shape (10-12 steps) it is
 // 4.6 % faster at d = 64 and about 1 % slower at d = 128 (four runs, each
 // within about 1 % noise); at d = 128 units of 4-8 steps come out even and
 // 36-step units at window 2048 6-10 % slower.  For units of at most
@@ -2783,7 +2798,7 @@ int64_t short_unit_steps(int head_dim)
 int units_per_wg(const FwdArgs &a, int kind, int nw, int64_t units, int32_t max_item_tiles,
                  int head_dim)
 {
-    if (kind != TA_KIND_TRIANGLE || nw < 5 || units > INT32_MAX ||
+    if (kind != TA_KIND_TRIANGLE || nw < 6 || a.group == 6 || units > INT32_MAX ||
         a.total_tokens >= kMaxUnitsTokens || max_item_tiles < 1)
         return 1;
     const int64_t unit_steps = (int64_t)max_item_tiles * (a.tile / kStep);
@@ -2809,28 +2824,41 @@ ta_status launch_tiles(int kind, const FwdArgs &a_in, int32_t head_dim,
     if (a_in.n_items <= 0)
         return TA_OK;
     FwdArgs a = a_in;
-    const int nw = a.group * a.rows_per_wg / 32;
+    // Compute waves of a workgroup: at most four row blocks (group 1, and
+    // group 2 at 64-row tiles) fit one workgroup of so many waves, two to a
+    // CU; group 7 leaves the eighth wave to copy; all others take eight, the
+    // row blocks shared out evenly (a second workgroup of two blocks would
+    // take as long as one of eight).
+    const int blocks = a.group * (a.tile / 32);
+    const int nw = blocks <= 4 ? blocks : a.group == 7 ? 7 : 8;
+    if (nw == 8) {
+        a.subtiles = (blocks + 7) / 8;
+        a.blocks_per_wg = (blocks + a.subtiles - 1) / a.subtiles;
+    }
+    const int units_nw = a.group * a.rows_per_wg / 32;  // of the multi-unit kernel
     const int64_t units = (int64_t)a.n_items * a.subtiles;
     hipError_t err;
-    const int ks_subtiles = (a.group * (a.tile / 32) + 3) / 4;  // four row blocks each
+    const int ks_subtiles = (blocks + 3) / 4;  // four row blocks each
     a.key_split = use_key_split(a, info, nw, ks_subtiles);
-    // Triangle passes over workgroups of five to eight waves run several
+    // Triangle passes over workgroups of six to eight waves run several
     // units per workgroup (multi-unit kernel); the others one.
     const int upw =
-        a.key_split ? 1 : units_per_wg(a, kind, nw, units, info->max_item_tiles, head_dim);
+        a.key_split ? 1 : units_per_wg(a, kind, units_nw, units, info->max_item_tiles, head_dim);
     if (upw > 1) {
         a.n_units = (int32_t)units;
         a.upw = upw;
         a.n_slots = (int32_t)((units + upw - 1) / upw);
         dim3 grid((unsigned)((int64_t)a.n_slots * a.hkv));
-        err = head_dim == 128 ? launch_units<128>(nw, grid, a, kind, stream)
-                              : launch_units<64>(nw, grid, a, kind, stream);
+        err = head_dim == 128 ? launch_units<128>(units_nw, grid, a, kind, stream)
+                              : launch_units<64>(units_nw, grid, a, kind, stream);
     } else {
-        if (a.key_split)
+        if (a.key_split) {
             a.subtiles = ks_subtiles;
+            a.blocks_per_wg = 4;
+        }
         const int64_t wgs = (int64_t)a.n_items * a.subtiles * a.hkv;
-        a.lead_span = lead_slots(info, a.key_split ? kKeySplitCost : tile_cost(nw),
-                                 a.key_split || nw <= 4, wgs);
+        const LaunchCost cost = a.key_split ? kKeySplitCost : tile_cost(nw, a.blocks_per_wg);
+        a.lead_span = lead_slots(info, cost, a.key_split || nw <= 4, wgs);
         a.n_lead = a.lead_span > 0 ? info->n_last_items : 0;
         dim3 grid((unsigned)wgs);
         err = head_dim == 128 ? launch_tile<128>(nw, grid, a, kind, stream)

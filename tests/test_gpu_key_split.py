@@ -35,6 +35,8 @@ CASES = [
     ("triangle", [0, 64, 900], 4, 2, 64, 130, 65, 129, 128, 3),   # sink not aligned, splits
     ("triangle", [0, 1000], 8, 1, 128, 16, 1, 200, 128, 8),       # splits without steps
     ("triangle", [0, 2000], 6, 1, 128, 0, 320, 0, 128, 0),        # no Last rows, no sink
+    ("triangle", [0, 930], 12, 2, 64, 8, 300, 70, 128, 0),        # G 6: 24 row blocks
+    ("causal", [0, 300, 397], 10, 2, 128, 0, 1, 0, 64, 0),        # G 5, T 64: 10 blocks
 ]
 
 

@@ -325,7 +325,7 @@ constexpr int phase_reads(int i, int count)
 // give a copy two whole phases to land, since each phase here uses another
 // step's tiles.
 template <int D, int NW, bool COPIER = false, bool LIST = false, bool KS = false>
-__global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void attn_tile_kernel(FwdArgs a,
+__global__ __launch_bounds__(NW * 64, NW == 4 ? (D == 64 ? 3 : 2) : 1) void attn_tile_kernel(FwdArgs a,
                                                                                int32_t kind)
 {
     constexpr int ROW_BYTES = 2 * D;
@@ -342,14 +342,28 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void attn_tile_kernel(Fwd
     static_assert(!KS || (NW == 8 && !COPIER), "two groups of four waves");
     constexpr int NC = COPIER ? NW - 1 : NW;  // compute waves
     constexpr int NB = KS ? NW / 2 : NW;      // row blocks (Q tiles)
+    // At d = 64 the softmax phase is the longer one (half the MFMAs per exp2),
+    // so two waves per SIMD leave its issue slots idle at barriers and waits:
+    // a step of an eight-wave workgroup takes about as long as at d = 128.
+    // Without the read-ahead across phases the four-wave form needs 168
+    // registers instead of 186, which lets three workgroups (three waves per
+    // SIMD, 32 KB of LDS each) share a CU.  It serves every group, four
+    // row blocks to a workgroup; each K/V tile copied then serves half the
+    // rows, which L2 carries.  Eight-wave (group 7: copier) form against it,
+    // same outputs bit for bit: window 2048, 65536 tokens, 32 heads over 8
+    // 1421 -> 1363 us; 48000 tokens, 28 over 4 940 -> 863; multi-head 32768
+    // tokens (four waves before, two to a CU) 754 -> 707; window 512, 65536
+    // tokens 594 -> 558; causal 8000 tokens, 40 over 8 377 -> 345; 32768
+    // tokens, 32 over 8 4363 -> 4347 (of many steps each: even).
+    constexpr bool LEAN = D == 64 && NW == 4;
     // An item's row blocks (32 rows of one head) are dealt out head first
     // (block b: head b % G, rows 32 (b / G)..), blocks_per_wg to a workgroup,
-    // by the key-split form and by the eight-wave one, so that eight waves
-    // serve any group: groups of 5 and 6 take three workgroups of a 128-row
+    // by the key-split, the eight-wave and the d = 64 four-wave form, so that
+    // they serve any group: groups of 5 and 6 take three workgroups of a 128-row
     // tile instead of four of five or six waves (24000 tokens, window 2048:
     // 1266 to 1003 and 1359 to 1124 us).  The other forms take R rows of
     // every head.
-    constexpr bool BLOCKS = KS || (NW == 8 && !COPIER);
+    constexpr bool BLOCKS = KS || LEAN || (NW == 8 && !COPIER);
     constexpr int N_COPY_WAVES = COPIER ? 1 : NW - NW / 2;
     constexpr int COPIES = (N_DMA + N_COPY_WAVES - 1) / N_COPY_WAVES;  // per tile
     constexpr int QK_STEPS = D / 16;
@@ -1417,7 +1431,7 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void attn_tile_kernel(Fwd
             // landed before the phase in which group 1 runs X(j - 1): the
             // first K fragments of M(j) are read at the start of that phase
             // (not with a copier wave, where it measured slower).
-            constexpr bool PRE = !COPIER;
+            constexpr bool PRE = !COPIER && !LEAN;
             if constexpr (PRE)
                 prefetch_k(0);
             end_phase(false);
@@ -2526,8 +2540,18 @@ hipError_t launch_tile_as(int nw, dim3 grid, const FwdArgs &a, int kind, hipStre
     case 2: hipLaunchKernelGGL((attn_tile_kernel<D, 2, false, LIST>), grid, dim3(128), 0, s, a, kind); break;
     case 4: hipLaunchKernelGGL((attn_tile_kernel<D, 4, false, LIST>), grid, dim3(256), 0, s, a, kind); break;
     // seven compute waves and a copier wave
-    case 7: hipLaunchKernelGGL((attn_tile_kernel<D, 8, true, LIST>), grid, dim3(512), 0, s, a, kind); break;
-    case 8: hipLaunchKernelGGL((attn_tile_kernel<D, 8, false, LIST>), grid, dim3(512), 0, s, a, kind); break;
+    case 7:
+        if constexpr (D == 128)
+            hipLaunchKernelGGL((attn_tile_kernel<D, 8, true, LIST>), grid, dim3(512), 0, s, a, kind);
+        else
+            return hipErrorInvalidValue;  // d = 64 runs four waves
+        break;
+    case 8:
+        if constexpr (D == 128)
+            hipLaunchKernelGGL((attn_tile_kernel<D, 8, false, LIST>), grid, dim3(512), 0, s, a, kind);
+        else
+            return hipErrorInvalidValue;
+        break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -2663,7 +2687,9 @@ struct LaunchCost {
     }
 };
 // Workgroups of at most four waves run two to a CU, at nearly the speed of
-// one each; one of five row blocks takes its steps a little faster than a
+// one each (three at d = 64, where the same figures choose well: 2000 tokens,
+// 32 heads over 8 34.6 -> 29.2 us, 5000 tokens, 20 over 4, 64-row tiles 107 ->
+// 87); one of five row blocks takes its steps a little faster than a
 // full one.
 LaunchCost tile_cost(int nw, int blocks_per_wg)
 {
@@ -2828,15 +2854,19 @@ ta_status launch_tiles(int kind, const FwdArgs &a_in, int32_t head_dim,
     // group 2 at 64-row tiles) fit one workgroup of so many waves, two to a
     // CU; group 7 leaves the eighth wave to copy; all others take eight, the
     // row blocks shared out evenly (a second workgroup of two blocks would
-    // take as long as one of eight).
+    // take as long as one of eight).  At d = 64 all take four, three
+    // workgroups to a CU (up to 8 % faster at group 4, 24 % at group 5; group
+    // 7 at 64-row tiles, whose 14 blocks leave two waves idle, is even).
     const int blocks = a.group * (a.tile / 32);
-    const int nw = blocks <= 4 ? blocks : a.group == 7 ? 7 : 8;
-    if (nw == 8) {
-        a.subtiles = (blocks + 7) / 8;
+    const bool lean = head_dim == 64 && blocks >= 4;
+    const int nw = lean ? 4 : blocks <= 4 ? blocks : a.group == 7 ? 7 : 8;
+    const int units_subtiles = a.subtiles;  // of the multi-unit kernel
+    if (lean || nw == 8) {
+        a.subtiles = (blocks + nw - 1) / nw;
         a.blocks_per_wg = (blocks + a.subtiles - 1) / a.subtiles;
     }
     const int units_nw = a.group * a.rows_per_wg / 32;  // of the multi-unit kernel
-    const int64_t units = (int64_t)a.n_items * a.subtiles;
+    const int64_t units = (int64_t)a.n_items * units_subtiles;
     hipError_t err;
     const int ks_subtiles = (blocks + 3) / 4;  // four row blocks each
     a.key_split = use_key_split(a, info, nw, ks_subtiles);
@@ -2845,6 +2875,7 @@ ta_status launch_tiles(int kind, const FwdArgs &a_in, int32_t head_dim,
     const int upw =
         a.key_split ? 1 : units_per_wg(a, kind, units_nw, units, info->max_item_tiles, head_dim);
     if (upw > 1) {
+        a.subtiles = units_subtiles;
         a.n_units = (int32_t)units;
         a.upw = upw;
         a.n_slots = (int32_t)((units + upw - 1) / upw);

@@ -37,6 +37,11 @@ CASES = [
     ("triangle", [0, 2000], 6, 1, 128, 0, 320, 0, 128, 0),        # no Last rows, no sink
     ("triangle", [0, 930], 12, 2, 64, 8, 300, 70, 128, 0),        # G 6: 24 row blocks
     ("causal", [0, 300, 397], 10, 2, 128, 0, 1, 0, 64, 0),        # G 5, T 64: 10 blocks
+    # d 64, whose plain form runs four-wave workgroups of dealt row blocks
+    ("causal", [0, 300, 397], 10, 2, 64, 0, 1, 0, 64, 0),         # 4, 4 and 2 blocks
+    ("triangle", [0, 933], 7, 1, 64, 8, 130, 70, 64, 0),          # G 7: 4, 4, 4 and 2 blocks
+    ("triangle", [0, 33, 1201], 7, 1, 64, 8, 130, 150, 128, 3),   # G 7, T 128: 28 blocks
+    ("triangle", [0, 700], 3, 3, 64, 0, 65, 40, 128, 0),          # G 1: 128 rows of a head
 ]
 
 

@@ -2804,25 +2804,22 @@ hipError_t launch_units(int nw, dim3 grid, const FwdArgs &a, int kind, hipStream
 // epilogue's normalisation, staging and stores beside the other group's
 // MFMAs), the single-unit kernel reads K ahead where the multi-unit kernel
 // has no registers to, and the pass runs at a power-limited clock, so the
-// multi-unit kernel pays off only for short units, and less at d = 128 than
-// at d = 64 (and not at all for groups of 5 and 6, whose row blocks fill eight
+// multi-unit kernel pays off only for short units (and not at all for groups of 5 and 6, whose row blocks fill eight
 // waves in the single-unit kernel only: 24000 tokens, sink 64, window 128,
-// group 6: 282 us in units of six waves, 241 without): on the paper's sink 8 / window 512 shape (10-12 steps) it is
-// 4.6 % faster at d = 64 and about 1 % slower at d = 128 (four runs, each
-// within about 1 % noise); at d = 128 units of 4-8 steps come out even and
-// 36-step units at window 2048 6-10 % slower.  For units of at most
-// short_unit_steps(d) steps: one workgroup per CU (256 CUs over the kv
+// group 6: 282 us in units of six waves, 241 without): at d = 128 units of 4-8
+// steps come out even, 10-12 steps (sink 8, window 512) 1 % slower and 36
+// steps (window 2048) 6-10 %; at d = 64, whose single-unit kernel runs three
+// four-wave workgroups to a CU, 6 steps even (65536 tokens, 32 heads over 8,
+// sink 64, window 128: 289 us, 292 single-unit), 10 steps 9 % slower (24000
+// tokens, 32 over 4, window 300: 150 us, 137 single-unit).  For units of at most
+// kShortUnitSteps steps: one workgroup per CU (256 CUs over the kv
 // heads) when its units' steps fit the LDS step table, otherwise the fewest
 // rounds of such workgroups whose units fit.  The environment variable
 // TRIATTN_UNITS_PER_WG, read at every launch, overrides the count (1: the
 // single-unit kernel, never in its key-split form) within the table limits:
 // for tests and tuning.
-int64_t short_unit_steps(int head_dim)
-{
-    return head_dim == 128 ? 8 : 16;
-}
-int units_per_wg(const FwdArgs &a, int kind, int nw, int64_t units, int32_t max_item_tiles,
-                 int head_dim)
+constexpr int64_t kShortUnitSteps = 8;
+int units_per_wg(const FwdArgs &a, int kind, int nw, int64_t units, int32_t max_item_tiles)
 {
     if (kind != TA_KIND_TRIANGLE || nw < 6 || a.group == 6 || units > INT32_MAX ||
         a.total_tokens >= kMaxUnitsTokens || max_item_tiles < 1)
@@ -2834,7 +2831,7 @@ int units_per_wg(const FwdArgs &a, int kind, int nw, int64_t units, int32_t max_
         if (forced >= 1)
             return (int)std::max<int64_t>(1, std::min<int64_t>(forced, cap));
     }
-    if (cap < 2 || unit_steps > short_unit_steps(head_dim))
+    if (cap < 2 || unit_steps > kShortUnitSteps)
         return 1;
     const int64_t slots = std::max<int64_t>(1, 256 / a.hkv);
     for (int64_t rounds = 1;; ++rounds) {
@@ -2873,7 +2870,7 @@ ta_status launch_tiles(int kind, const FwdArgs &a_in, int32_t head_dim,
     // Triangle passes over workgroups of six to eight waves run several
     // units per workgroup (multi-unit kernel); the others one.
     const int upw =
-        a.key_split ? 1 : units_per_wg(a, kind, units_nw, units, info->max_item_tiles, head_dim);
+        a.key_split ? 1 : units_per_wg(a, kind, units_nw, units, info->max_item_tiles);
     if (upw > 1) {
         a.subtiles = units_subtiles;
         a.n_units = (int32_t)units;

@@ -91,7 +91,6 @@ struct FwdArgs {
     // schedule order)
     int32_t n_lead;
     int32_t lead_span;
-    int32_t key_split;    // the key-split form of the tile kernel
     // every Last q-tile has one split, which covers its keys: its rows go
     // straight to O and LSE, and no merge follows
     int32_t direct;
@@ -314,17 +313,7 @@ constexpr int phase_reads(int i, int count)
 // issue no copies.
 // LIST: the kernel serves block-sparse schedules, whose list items read
 // their k-tiles from the schedule's list section (the other kinds have none).
-// KS (key split): the two ping-pong groups own the same four row blocks (32
-// rows of one head each) and take the steps of the item in turn, group g
-// steps 2j + g, so an item's serial chain of steps is half as long; their
-// partial results are combined through LDS at the end.  For launches too
-// small to fill the chip, which are bound by that chain: two consecutive
-// steps take 2900 cycles instead of 4950 (d = 128, steady state).  The row
-// blocks of an item are dealt out head first, four to a workgroup, whatever
-// the group, so no wave idles for groups of 5 to 7 either.  Four K/V stages
-// give a copy two whole phases to land, since each phase here uses another
-// step's tiles.
-template <int D, int NW, bool COPIER = false, bool LIST = false, bool KS = false>
+template <int D, int NW, bool COPIER = false, bool LIST = false>
 __global__ __launch_bounds__(NW * 64, NW == 4 ? (D == 64 ? 3 : 2) : 1) void attn_tile_kernel(FwdArgs a,
                                                                                int32_t kind)
 {
@@ -332,16 +321,14 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? (D == 64 ? 3 : 2) : 1) void attn
     constexpr int CHUNKS = D / 8;                       // 16-byte chunks per row
     constexpr int TILE_BYTES = kStep * ROW_BYTES;       // one K or V tile
     constexpr int STAGE_BYTES = 2 * TILE_BYTES;         // K tile, then V tile
-    constexpr int N_STAGES = KS ? 4 : 2;                // LDS ring
+    constexpr int N_STAGES = 2;                         // LDS double buffer
     constexpr int ROWS_PER_DMA = 1024 / ROW_BYTES;      // rows per wave copy
     constexpr int N_DMA = kStep / ROWS_PER_DMA;         // wave copies per tile
     // Only the waves of ping-pong group 0 copy K/V tiles into LDS, spread
     // over the MFMAs of their matrix phase (see the phase loop below), or
     // the copier wave alone.
     static_assert(!COPIER || NW == 8, "a copier wave beside seven compute waves");
-    static_assert(!KS || (NW == 8 && !COPIER), "two groups of four waves");
     constexpr int NC = COPIER ? NW - 1 : NW;  // compute waves
-    constexpr int NB = KS ? NW / 2 : NW;      // row blocks (Q tiles)
     // At d = 64 the softmax phase is the longer one (half the MFMAs per exp2),
     // so two waves per SIMD leave its issue slots idle at barriers and waits:
     // a step of an eight-wave workgroup takes about as long as at d = 128.
@@ -358,12 +345,12 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? (D == 64 ? 3 : 2) : 1) void attn
     constexpr bool LEAN = D == 64 && NW == 4;
     // An item's row blocks (32 rows of one head) are dealt out head first
     // (block b: head b % G, rows 32 (b / G)..), blocks_per_wg to a workgroup,
-    // by the key-split, the eight-wave and the d = 64 four-wave form, so that
-    // they serve any group: groups of 5 and 6 take three workgroups of a 128-row
+    // by the eight-wave and the d = 64 four-wave form, so that they serve any
+    // group: groups of 5 and 6 take three workgroups of a 128-row
     // tile instead of four of five or six waves (24000 tokens, window 2048:
     // 1266 to 1003 and 1359 to 1124 us).  The other forms take R rows of
     // every head.
-    constexpr bool BLOCKS = KS || LEAN || (NW == 8 && !COPIER);
+    constexpr bool BLOCKS = LEAN || (NW == 8 && !COPIER);
     constexpr int N_COPY_WAVES = COPIER ? 1 : NW - NW / 2;
     constexpr int COPIES = (N_DMA + N_COPY_WAVES - 1) / N_COPY_WAVES;  // per tile
     constexpr int QK_STEPS = D / 16;
@@ -381,9 +368,8 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? (D == 64 ? 3 : 2) : 1) void attn
     // two waves (the two of one workgroup's ping-pong pair sit on different
     // SIMDs).
     constexpr int QTILE_BYTES = 32 * ROW_BYTES;
-    constexpr bool Q_IN_STAGE = NB * QTILE_BYTES <= STAGE_BYTES;
+    constexpr bool Q_IN_STAGE = NW * QTILE_BYTES <= STAGE_BYTES;
     constexpr int QREGION = (Q_IN_STAGE ? N_STAGES - 1 : N_STAGES) * STAGE_BYTES;
-    static_assert(!KS || Q_IN_STAGE, "the key-split form keeps Q in its last stage");
     __shared__ __attribute__((aligned(1024))) unsigned char
         smem[N_STAGES * STAGE_BYTES + (Q_IN_STAGE ? 0 : NW * QTILE_BYTES)];
     static_assert(sizeof(smem) + (LIST ? kKeyTable * 4 : 0) <= 160 * 1024, "LDS of a CU");
@@ -464,10 +450,9 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? (D == 64 ? 3 : 2) : 1) void attn
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int half = lane >> 5;
     const int col = lane & 31;
-    const int block = KS ? wave % NB : wave;  // the wave's Q tile
     int head, row_base;
     if constexpr (BLOCKS) {
-        const int b = a.blocks_per_wg * sub + block;
+        const int b = a.blocks_per_wg * sub + wave;
         head = g * a.group + b % a.group;
         row_base = r0 + 32 * (b / a.group);
     } else {
@@ -475,7 +460,7 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? (D == 64 ? 3 : 2) : 1) void attn
         head = g * a.group + wave / waves_per_head;
         row_base = wr0 + (wave % waves_per_head) * 32;
     }
-    const bool wave_active = row_base < r1 && (!BLOCKS || block < a.blocks_per_wg);
+    const bool wave_active = row_base < r1 && (!BLOCKS || wave < a.blocks_per_wg);
     const int my_row = row_base + col;            // sequence-relative row
     const bool row_valid = my_row < r1;
     const int row_hi = (r1 - 1 < row_base + 31) ? r1 - 1 : row_base + 31;
@@ -537,22 +522,18 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? (D == 64 ? 3 : 2) : 1) void attn
     if (!COPIER || wave < NC) {
         const uint16_t *qb = a.q + ((seq_off + q_row0) * a.hq + head) * (int64_t)D;
         const uint32_t q_pitch = (uint32_t)(a.hq * ROW_BYTES);
-        // a key-split pair of waves copies half of their tile each
-        constexpr int Q_COPIES = QTILE_BYTES / 1024 / (KS ? 2 : 1);
-        const int q_first = KS ? (wave / NB) * Q_COPIES : 0;
 #pragma unroll
-        for (int ii = 0; ii < Q_COPIES; ++ii) {
-            const int i = q_first + ii;
+        for (int i = 0; i < QTILE_BYTES / 1024; ++i) {
             const int row = i * (1024 / ROW_BYTES) + lane / CHUNKS;
             const int rr = min(row_base + row, r1 - 1) - q_row0;  // 0 .. 31
             const uint32_t off = __umul24((uint32_t)rr, q_pitch) +
                                  (uint32_t)(((lane % CHUNKS) ^ kswz<D>(row)) << 4);
-            copy_to_lds16(qb, off, smem_addr + QREGION + block * QTILE_BYTES + i * 1024);
+            copy_to_lds16(qb, off, smem_addr + QREGION + wave * QTILE_BYTES + i * 1024);
         }
     }
     bf16x8 qf[QK_STEPS];
     auto read_q = [&]() TA_INLINE {
-        const unsigned char *qt = smem + QREGION + block * QTILE_BYTES + col * ROW_BYTES;
+        const unsigned char *qt = smem + QREGION + wave * QTILE_BYTES + col * ROW_BYTES;
 #pragma unroll
         for (int s = 0; s < QK_STEPS; ++s)
             qf[s] = *reinterpret_cast<const bf16x8 *>(qt + (((2 * s + half) ^ kswz<D>(col)) << 4));
@@ -567,8 +548,8 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? (D == 64 ? 3 : 2) : 1) void attn
     // l / CHUNKS, stored chunk l % CHUNKS, which holds logical chunk
     // (l % CHUNKS) ^ swizzle(row).  Copy waves (group 0, wave w < N_COPY_WAVES)
     // own copies m = w, w + N_COPY_WAVES, ... of every K and V tile.
-    const bool copy_wave = COPIER ? wave == NW - 1 : KS || wave < N_COPY_WAVES;
-    const int copy_rank = COPIER ? 0 : block;  // the wave's first copy number
+    const bool copy_wave = COPIER ? wave == NW - 1 : wave < N_COPY_WAVES;
+    const int copy_rank = COPIER ? 0 : wave;  // the wave's first copy number
     const int dma_row_in = lane / CHUNKS;
     const int dma_pc = lane % CHUNKS;
     // The swizzle of row m * ROWS_PER_DMA + i is swizzle(i) ^ swizzle of the
@@ -987,10 +968,7 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? (D == 64 ? 3 : 2) : 1) void attn
         __builtin_amdgcn_sched_barrier(0);
     };
     auto do_x = [&](int j) TA_INLINE {
-        // an odd number of steps leaves the key-split form one step without
-        // kept keys: its keys lie past every row (their V rows are those of
-        // the last step, so that 0 * V is 0)
-        const int key0 = KS && j >= nsteps ? wr_last + 1 : step_key0(j);
+        const int key0 = step_key0(j);
         // the step crosses its rows' diagonal, or a window edge
         const bool need_causal = key0 + kStep - 1 > row_base;
         const bool need_window = mode == kModeStreaming && key0 + kStep - 1 >= a.sink &&
@@ -1086,245 +1064,6 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? (D == 64 ? 3 : 2) : 1) void attn
             return;
         }
     }
-    if constexpr (KS) {
-        if (nsteps > 0) {
-            // Phase p runs step p of the item: its group's matrix phase reads
-            // K(p) and V(p - 2) from stage p & 3, while the other group runs
-            // its softmax.  During phase p the matrix group copies K(p + 3)
-            // and V(p + 1) into stage (p + 3) & 3 (last read in phase p - 1)
-            // and waits for them at the end of its softmax phase p + 1, so
-            // they have landed a whole phase before phase p + 3: the first K
-            // fragments of every matrix phase are read in the softmax phase
-            // before it.  The prologue copies K(0..2) and V(0); Q sits in
-            // stage 3 until every wave has read it.
-            auto key_at = [&](int s) TA_INLINE { return step_key0(min(s, nsteps - 1)); };
-            auto issue_tile = [&](const TileCopy &t, bool is_v) TA_INLINE {
-#pragma unroll
-                for (int i = 0; i < COPIES; ++i)
-                    issue_copy(t, i, is_v);
-            };
-            issue_tile(plan_copy(kbase, key_at(group), group, false), false);
-            if (group == 0)
-                issue_tile(plan_copy(vbase, key_at(0), 2, true), true);
-            else
-                issue_tile(plan_copy(kbase, key_at(2), 2, false), false);
-            __builtin_amdgcn_sched_barrier(0);
-            wait_vmcnt(COPIES * (N_DMA % N_COPY_WAVES == 0));  // Q and K(0), K(1)
-            end_phase(false);
-            read_q();
-            end_phase(false);  // every wave has read its Q: stage 3 is free
-            const int pairs = (nsteps + 1) / 2;
-            auto run = [&](auto grp, auto burst) TA_INLINE {
-                constexpr int G0 = decltype(grp)::value;
-                constexpr bool B = decltype(burst)::value;
-                uint32_t bk[B ? COPIES : 1], bv[B ? COPIES : 1];
-                if constexpr (B) {
-#pragma unroll
-                    for (int i = 0; i < COPIES; ++i) {
-                        // row >= i * ROWS_PER_DMA rows of at least 1024 / ROWS_PER_DMA
-                        // bytes each, so subtracting i KB cannot wrap
-                        const int row = (copy_rank * COPIES + i) * ROWS_PER_DMA + dma_row_in;
-                        const uint32_t ro = __umul24((uint32_t)row, row_stride_bytes) -
-                                            (uint32_t)(i * 1024);
-                        bk[i] = ro + (uint32_t)((dma_pc ^ kswz<D>(row)) << 4);
-                        bv[i] = ro + (uint32_t)((dma_pc ^ vswz<D>(row)) << 4);
-                    }
-                }
-                auto hook = [&](int slot) TA_INLINE {
-                    if constexpr (B) {
-                        if (slot == BURST_K_SLOT)
-                            copy_burst_to_lds16<COPIES>(cp_k.base, bk, cp_k.lds + burst_lds);
-                        else if (slot == BURST_V_SLOT)
-                            copy_burst_to_lds16<COPIES>(cp_v.base, bv, cp_v.lds + burst_lds);
-                    } else {
-                        copy_hook(slot);
-                    }
-                };
-                // the copies of phase p, whose stage is st
-                auto prep = [&](int p, auto st) TA_INLINE {
-                    constexpr int dst = (decltype(st)::value + 3) & 3;
-                    cp_k = plan_copy(kbase, key_at(p + 3), dst, false);
-                    cp_v = plan_copy(vbase, key_at(p + 1), dst, true);
-                };
-                using StA = std::integral_constant<int, G0>;
-                using StB = std::integral_constant<int, G0 + 2>;
-                if constexpr (G0 == 1)
-                    end_phase(true);  // phase 0: K(1) and K(2) have landed
-                do_m(StA{}, true, false, hook, std::false_type{},
-                     [&]() TA_INLINE { prep(G0, StA{}); });
-                // copies whose slot lies past the QK^T MFMAs
-                if constexpr (B) {
-                    if constexpr (BURST_V_SLOT >= 2 * QK_STEPS)
-                        copy_burst_to_lds16<COPIES>(cp_v.base, bv, cp_v.lds + burst_lds);
-                } else {
-#pragma unroll
-                    for (int c = 0; c < 2 * COPIES; ++c)
-                        if (c * COPY_STRIDE + COPY_STRIDE - 1 >= 2 * QK_STEPS)
-                            issue_slot(c);
-                }
-                end_phase(false);
-                auto step = [&](int j, auto st) TA_INLINE {
-                    prefetch_k(decltype(st)::value);
-                    do_x(2 * (j - 1) + G0);
-                    end_phase(true);
-                    do_m(st, true, true, hook, std::true_type{},
-                         [&]() TA_INLINE { prep(2 * j + G0, st); });
-                    end_phase(false);
-                };
-                int j = 1;
-                for (; j + 1 < pairs; j += 2) {
-                    step(j, StB{});
-                    step(j + 1, StA{});
-                }
-                if (j < pairs)
-                    step(j, StB{});
-                do_x(2 * (pairs - 1) + G0);
-                end_phase(true);
-                do_m((2 * pairs + G0) & 3, false, true, no_hook, std::false_type{}, no_prep);
-                end_phase(false);
-                if constexpr (G0 == 0)
-                    end_phase(false);
-            };
-            // The steps' keys increase, so every tile lies inside the
-            // sequence when the last step's does.
-            const bool inside = step_key0(nsteps - 1) + kStep - 1 <= key_max;
-            using G0 = std::integral_constant<int, 0>;
-            using G1 = std::integral_constant<int, 1>;
-            if (group == 0) {
-                if (BURST && inside)
-                    run(G0{}, std::bool_constant<BURST>{});
-                else
-                    run(G0{}, std::false_type{});
-            } else {
-                if (BURST && inside)
-                    run(G1{}, std::bool_constant<BURST>{});
-                else
-                    run(G1{}, std::false_type{});
-            }
-        } else {
-            wait_vmcnt(0);  // no steps: the Q copies must still land
-            barrier_no_fence();
-        }
-
-        // Combine the two groups' partial results: each wave hands half of
-        // its O (and its m and l) to the other wave of its pair through LDS
-        // and finishes the other half, d = group * D / 2 .. of its rows.
-        constexpr int HB = D_BLOCKS / 2;       // 32-wide d blocks of a half
-        constexpr int XB = HB * 16 * 64 * 4;   // bytes of a wave's half of O
-        static_assert(NW * XB + NW * 64 * 4 <= (int)sizeof(smem), "exchange fits the stages");
-        const float l_own = pair_sum(l_run);
-        unsigned char *xo = smem + wave * XB;
-        float *xm = reinterpret_cast<float *>(smem + NW * XB);
-        auto give = [&](auto first) TA_INLINE {
-#pragma unroll
-            for (int b = 0; b < HB; ++b)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    f32x4 t;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        t[e] = oacc[decltype(first)::value + b][4 * j + e];
-                    *reinterpret_cast<f32x4 *>(xo + (b * 4 + j) * 1024 + lane * 16) = t;
-                }
-        };
-        if (group == 0)
-            give(std::integral_constant<int, HB>{});
-        else
-            give(std::integral_constant<int, 0>{});
-        xm[wave * 64 + lane] = half == 0 ? m_ref : l_own;
-        barrier_no_fence();
-        const int mate = wave ^ NB;
-        const float m_oth = xm[mate * 64 + col], l_oth = xm[mate * 64 + 32 + col];
-        const float m_max = fmaxf(m_ref, m_oth);
-        const float m_use = (m_max == -INFINITY) ? 0.f : m_max;
-        const float w_own = __builtin_amdgcn_exp2f(m_ref - m_use);
-        const float w_oth = __builtin_amdgcn_exp2f(m_oth - m_use);
-        const float l_tot = w_own * l_own + w_oth * l_oth;
-        const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
-        const float row_lse = l_tot > 0.f ? (m_use + __log2f(l_tot)) * kLn2 : -INFINITY;
-        unsigned char *xi = smem + mate * XB;
-        f32x16 res[HB];
-        auto take = [&](auto first) TA_INLINE {
-#pragma unroll
-            for (int b = 0; b < HB; ++b)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const f32x4 t =
-                        *reinterpret_cast<const f32x4 *>(xi + (b * 4 + j) * 1024 + lane * 16);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        res[b][4 * j + e] =
-                            (w_own * oacc[decltype(first)::value + b][4 * j + e] +
-                             w_oth * t[e]) * inv;
-                }
-        };
-        if (group == 0)
-            take(std::integral_constant<int, 0>{});
-        else
-            take(std::integral_constant<int, HB>{});
-        if (!wave_active)
-            return;
-        // Whole pieces of the rows (D / 2 values each) are staged in the
-        // region the wave has just read (no other wave reads it), swizzled
-        // by 16-byte chunk, then stored.
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
-        asm volatile("" ::: "memory");
-        auto store_rows = [&](auto f32_tag, void *dst) TA_INLINE {
-            constexpr bool F32 = decltype(f32_tag)::value;
-            constexpr int PB = D / 2 * (F32 ? 4 : 2);  // bytes of a row piece
-            constexpr int CH = PB / 16;                // its 16-byte chunks
-            auto swz = [](int r) { return (r / (256 / PB)) & (CH - 1); };
-#pragma unroll
-            for (int b = 0; b < HB; ++b)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    f32x4 t;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        t[e] = res[b][4 * j + e];
-                    // values d = 32 b + 8 j + 4 half + e of the piece
-                    if constexpr (F32) {
-                        const int pc = (8 * b + 2 * j + half) ^ swz(col);
-                        *reinterpret_cast<f32x4 *>(xi + col * PB + pc * 16) = t;
-                    } else {
-                        const int pc = (4 * b + j) ^ swz(col);
-                        *reinterpret_cast<bf16x4 *>(xi + col * PB + pc * 16 + half * 8) =
-                            __builtin_convertvector(t, bf16x4);
-                    }
-                }
-            asm volatile("" ::: "memory");
-            __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
-            asm volatile("" ::: "memory");
-            unsigned char *out = static_cast<unsigned char *>(dst) + group * PB;
-            const int64_t pitch = (int64_t)a.hq * (2 * PB);
-#pragma unroll
-            for (int k = 0; k < 32 * CH / 64; ++k) {
-                const int rr = lane / CH + k * (64 / CH);
-                const int cc = lane % CH;
-                const u32x4 val =
-                    *reinterpret_cast<const u32x4 *>(xi + rr * PB + ((cc ^ swz(rr)) << 4));
-                if (row_base + rr < r1)
-                    *reinterpret_cast<u32x4 *>(out + rr * pitch + cc * 16) = val;
-            }
-        };
-        const bool lse_lane = group == 0 && half == 0 && row_valid;
-        if (part_base >= 0) {
-            const int64_t prow = (int64_t)(part_base + (row_base - r0)) * a.hq + head;
-            store_rows(std::true_type{}, a.part_o + prow * D);
-            if (lse_lane)
-                a.part_lse[prow + (int64_t)col * a.hq] = row_lse;
-            return;
-        }
-        const int64_t orow = ((seq_off + row_base) * a.hq + head) * (int64_t)D;
-        if (a.o_f32)
-            store_rows(std::true_type{}, reinterpret_cast<float *>(a.o) + orow);
-        else
-            store_rows(std::false_type{}, reinterpret_cast<uint16_t *>(a.o) + orow);
-        if (a.lse && lse_lane)
-            a.lse[(int64_t)head * a.total_tokens + seq_off + my_row] = row_lse;
-        return;
-    } else {  // every form but the key-split one, to the end of the kernel
     if (nsteps > 0) {
         // Prologue: the copy waves copy K(0) into stage 0.
         if (copy_wave) {
@@ -1561,7 +1300,6 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? (D == 64 ? 3 : 2) : 1) void attn
     }
     if (a.lse && half == 0)
         a.lse[(int64_t)head * a.total_tokens + seq_off + my_row] = row_lse;
-    }  // not the key-split form
 }
 
 // Multi-unit form of the tile kernel for workgroups of six to eight waves
@@ -2531,11 +2269,6 @@ int rows_per_wg(int group, int tile)
 template <int D, bool LIST>
 hipError_t launch_tile_as(int nw, dim3 grid, const FwdArgs &a, int kind, hipStream_t s)
 {
-    if (a.key_split) {
-        hipLaunchKernelGGL((attn_tile_kernel<D, 8, false, LIST, true>), grid, dim3(512), 0, s, a,
-                           kind);
-        return hipGetLastError();
-    }
     switch (nw) {
     case 2: hipLaunchKernelGGL((attn_tile_kernel<D, 2, false, LIST>), grid, dim3(128), 0, s, a, kind); break;
     case 4: hipLaunchKernelGGL((attn_tile_kernel<D, 4, false, LIST>), grid, dim3(256), 0, s, a, kind); break;
@@ -2664,7 +2397,6 @@ FwdArgs make_args(const void *q, const void *k, const void *v, void *o,
     a.n_units = 0;
     a.n_slots = 0;
     a.upw = 1;
-    a.key_split = 0;
     a.direct = 0;
     a.n_lead = 0;
     a.lead_span = 0;
@@ -2672,80 +2404,21 @@ FwdArgs make_args(const void *q, const void *k, const void *v, void *o,
 }
 
 // Device time of a launch, in units of 1000 cycles at d = 128, for choosing
-// between forms and orders of it: workgroups of `slots` at a time, each with
-// a fixed cost (schedule item, Q and the first K tile from memory, pipeline
-// fill, epilogue) and a cost per 64-key step; the longest bounds the pass
-// from below, and a pass of several rounds ends half a workgroup late on
-// average.
+// its order: workgroups of `slots` at a time, each with a fixed cost (schedule
+// item, Q and the first K tile from memory, pipeline fill, epilogue) and a
+// cost per 64-key step.
 struct LaunchCost {
     double fixed, step, slots;
     double wg(double steps) const { return fixed + step * steps; }
-    double pass(double wgs, double mean_steps, double max_steps) const
-    {
-        const double all = wgs > slots ? (wgs / slots + 0.5) * wg(mean_steps) : 0.0;
-        return std::max(wg(max_steps), all);
-    }
 };
 // Workgroups of at most four waves run two to a CU, at nearly the speed of
-// one each (three at d = 64, where the same figures choose well: 2000 tokens,
-// 32 heads over 8 34.6 -> 29.2 us, 5000 tokens, 20 over 4, 64-row tiles 107 ->
-// 87); one of five row blocks takes its steps a little faster than a
+// one each; one of five row blocks takes its steps a little faster than a
 // full one.
 LaunchCost tile_cost(int nw, int blocks_per_wg)
 {
     if (nw <= 4)
         return {10.0, 2.6, 512.0};
     return {10.0, blocks_per_wg == 5 ? 2.25 : 2.4, 256.0};
-}
-
-// The key-split form: a workgroup owns half as many row blocks for half as
-// many step times.
-constexpr LaunchCost kKeySplitCost = {11.0, 1.4, 256.0};
-
-// Items of a pass and their steps, as the choice of a form takes them.  For a
-// Triangle schedule they follow from the sections and the sequences with the
-// automatic split rule, whatever split count the schedule was built with, so
-// that a streaming row's result does not depend on the split count.
-struct PassShape {
-    double items, mean, longest;
-};
-PassShape pass_shape(const ta_schedule_info *info)
-{
-    const double T = info->tile, tps = T / kStep;
-    double items = info->n_items, longest = info->max_item_tiles;
-    if (info->kind == TA_KIND_TRIANGLE) {
-        const double streaming = std::ceil(info->sink / T) + std::ceil(info->window / T) + 1.0;
-        const double split = std::max(streaming, std::ceil(2048.0 / T));
-        const double seq = std::ceil((double)info->total_tokens / (T * std::max(info->batch, 1)));
-        items = (double)(info->n_items - info->n_last_items) +
-                info->n_merge_items * std::ceil(seq / split);
-        longest = std::min(info->n_merge_items > 0 ? split : streaming,
-                           info->batch == 1 ? seq : 2.0 * seq);
-    }
-    items = std::max(items, 1.0);
-    return {items, tps * (double)info->kept_tiles_per_qhead / items, tps * longest};
-}
-
-// Whether the pass runs in the key-split form: where the launch does not fill
-// the chip for long, its time is that of the longest items' steps, which the
-// form halves, and small workgroups leave no CU idle; over many rounds it
-// loses, since each K/V tile copied serves half the rows and the fixed costs
-// come twice as often.  The two costs were fitted to 150 launches of 300 to
-// 16384 tokens (head dimension 64 and 128, groups of 1 to 8, all kinds); the
-// choice they make is 0.15 % off the better form on average, where the plain
-// form alone is 14 % off and the key-split form alone 3 %.  Causal, 1723
-// tokens, 5 heads over one kv head: 37 against 23 us; 2048 tokens, 32 heads
-// over 8: 45 against 41; 3000 tokens: 75 against 82.  Near ties stay with the
-// plain form (0.97).
-bool use_key_split(const FwdArgs &a, const ta_schedule_info *info, int nw, int64_t ks_subtiles)
-{
-    if (std::getenv("TRIATTN_UNITS_PER_WG") ||
-        (int64_t)info->n_items * ks_subtiles * a.hkv > INT32_MAX)
-        return false;
-    const PassShape p = pass_shape(info);
-    const double rows = p.items * a.hkv;
-    return kKeySplitCost.pass(rows * (double)ks_subtiles, p.mean, p.longest) <
-           0.97 * tile_cost(nw, a.blocks_per_wg).pass(rows * a.subtiles, p.mean, p.longest);
 }
 
 // Launch slots over which a Triangle schedule's Last split items are spread
@@ -2816,8 +2489,7 @@ hipError_t launch_units(int nw, dim3 grid, const FwdArgs &a, int kind, hipStream
 // heads) when its units' steps fit the LDS step table, otherwise the fewest
 // rounds of such workgroups whose units fit.  The environment variable
 // TRIATTN_UNITS_PER_WG, read at every launch, overrides the count (1: the
-// single-unit kernel, never in its key-split form) within the table limits:
-// for tests and tuning.
+// single-unit kernel) within the table limits: for tests and tuning.
 constexpr int64_t kShortUnitSteps = 8;
 int units_per_wg(const FwdArgs &a, int kind, int nw, int64_t units, int32_t max_item_tiles)
 {
@@ -2865,12 +2537,9 @@ ta_status launch_tiles(int kind, const FwdArgs &a_in, int32_t head_dim,
     const int units_nw = a.group * a.rows_per_wg / 32;  // of the multi-unit kernel
     const int64_t units = (int64_t)a.n_items * units_subtiles;
     hipError_t err;
-    const int ks_subtiles = (blocks + 3) / 4;  // four row blocks each
-    a.key_split = use_key_split(a, info, nw, ks_subtiles);
     // Triangle passes over workgroups of six to eight waves run several
     // units per workgroup (multi-unit kernel); the others one.
-    const int upw =
-        a.key_split ? 1 : units_per_wg(a, kind, units_nw, units, info->max_item_tiles);
+    const int upw = units_per_wg(a, kind, units_nw, units, info->max_item_tiles);
     if (upw > 1) {
         a.subtiles = units_subtiles;
         a.n_units = (int32_t)units;
@@ -2880,13 +2549,8 @@ ta_status launch_tiles(int kind, const FwdArgs &a_in, int32_t head_dim,
         err = head_dim == 128 ? launch_units<128>(units_nw, grid, a, kind, stream)
                               : launch_units<64>(units_nw, grid, a, kind, stream);
     } else {
-        if (a.key_split) {
-            a.subtiles = ks_subtiles;
-            a.blocks_per_wg = 4;
-        }
         const int64_t wgs = (int64_t)a.n_items * a.subtiles * a.hkv;
-        const LaunchCost cost = a.key_split ? kKeySplitCost : tile_cost(nw, a.blocks_per_wg);
-        a.lead_span = lead_slots(info, cost, a.key_split || nw <= 4, wgs);
+        a.lead_span = lead_slots(info, tile_cost(nw, a.blocks_per_wg), nw <= 4, wgs);
         a.n_lead = a.lead_span > 0 ? info->n_last_items : 0;
         dim3 grid((unsigned)wgs);
         err = head_dim == 128 ? launch_tile<128>(nw, grid, a, kind, stream)

@@ -246,6 +246,27 @@ def test_packing_invariance():
             assert torch.equal(plse[:, s:e], alse), (kind, b)
 
 
+@pytest.mark.parametrize("hq,hkv,d,T", [(32, 8, 128, 128), (7, 1, 128, 64), (5, 1, 128, 128),
+                                        (32, 8, 64, 128), (4, 4, 64, 64), (4, 4, 128, 128)])
+def test_packing_invariance_in_a_full_launch(hq, hkv, d, T):
+    """Short sequences alone, whose few workgroups leave most of the chip
+    idle, against the same ones in a batch of several rounds of workgroups:
+    whatever form of the kernel each launch takes, the rows are the same bit
+    for bit."""
+    log(f"case packing hq={hq} hkv={hkv} d={d} T={T}")
+    lens = [333, 1, 1024] + [3000] * max(1, 40 // hkv) + [2001]
+    cu = [0] + [int(x) for x in np.cumsum(lens)]
+    q, k, v = _cuda(*draw_qkv(cu, hq, hkv, d, 16))
+    for kind in ("triangle", "causal"):
+        packed, plse, _ = run_pass(kind, q, k, v, cu, 32, 256, 100, T)
+        for b in (0, 1, 2, len(lens) - 1):
+            s, e = cu[b], cu[b + 1]
+            alone, alse, _ = run_pass(kind, *(t[s:e].contiguous() for t in (q, k, v)),
+                                      [0, e - s], 32, 256, 100, T)
+            assert torch.equal(packed[s:e], alone), (kind, b)
+            assert torch.equal(plse[:, s:e], alse), (kind, b)
+
+
 def test_determinism():
     cu = [0, 5000]
     q, k, v = _cuda(*draw_qkv(cu, 8, 2, 128, 7))

@@ -1,14 +1,9 @@
-"""GPU tests of the key-split form of the tile kernel: the two ping-pong
-groups of a workgroup own the same four row blocks and take the 64-key steps
-in turn, and their partial results are combined through LDS.
-
-The launches here are small, so the library chooses that form by its own
-rule; with TRIATTN_UNITS_PER_WG=1 the same call runs the plain form.  Sizes
-sit where the form can go wrong: one step, an odd number of steps (the last
-step of the second group then holds no kept key), row blocks of several heads
-with a remainder in the last workgroup, tiles of 64 rows whose workgroups are
-not full, ragged last tiles, tiles past the end of the sequence, list items,
-split items, both head dimensions and both output types."""
+"""GPU tests of the tile kernel's workgroups at the sizes where they can go
+wrong: one step, an odd number of steps, row blocks of several heads with a
+remainder in the last workgroup, tiles of 64 rows whose workgroups are not
+full, ragged last tiles, tiles past the end of the sequence, list items, split
+items, both head dimensions and both output types; and of the passes whose
+Last q-tiles have one split each, which run without a merge."""
 import math
 import os
 
@@ -37,7 +32,7 @@ CASES = [
     ("triangle", [0, 2000], 6, 1, 128, 0, 320, 0, 128, 0),        # no Last rows, no sink
     ("triangle", [0, 930], 12, 2, 64, 8, 300, 70, 128, 0),        # G 6: 24 row blocks
     ("causal", [0, 300, 397], 10, 2, 128, 0, 1, 0, 64, 0),        # G 5, T 64: 10 blocks
-    # d 64, whose plain form runs four-wave workgroups of dealt row blocks
+    # d 64: four-wave workgroups of dealt row blocks
     ("causal", [0, 300, 397], 10, 2, 64, 0, 1, 0, 64, 0),         # 4, 4 and 2 blocks
     ("triangle", [0, 933], 7, 1, 64, 8, 130, 70, 64, 0),          # G 7: 4, 4, 4 and 2 blocks
     ("triangle", [0, 33, 1201], 7, 1, 64, 8, 130, 150, 128, 3),   # G 7, T 128: 28 blocks
@@ -45,37 +40,27 @@ CASES = [
 ]
 
 
-def _run(plain, *args, **kw):
-    if plain:
-        os.environ[ENV] = "1"
-    try:
-        o, lse, _ = run_pass(*args, poison=True, **kw)
-        torch.cuda.synchronize()
-    finally:
-        os.environ.pop(ENV, None)
+def _run(*args, **kw):
+    o, lse, _ = run_pass(*args, poison=True, **kw)
+    torch.cuda.synchronize()
     return o, lse
 
 
 @pytest.mark.parametrize("kind,cu,hq,hkv,d,S,W,L,T,splits", CASES)
-def test_key_split(kind, cu, hq, hkv, d, S, W, L, T, splits):
-    log(f"case key split {kind} cu={cu} hq={hq} hkv={hkv} d={d} S={S} W={W} L={L} T={T}")
+def test_row_blocks(kind, cu, hq, hkv, d, S, W, L, T, splits):
+    log(f"case row blocks {kind} cu={cu} hq={hq} hkv={hkv} d={d} S={S} W={W} L={L} T={T}")
     q, k, v = draw_qkv(cu, hq, hkv, d, seed=31 + hq + S)
     args = [kind] + [t.cuda() for t in (q, k, v)] + [cu, S, W, L, T, splits]
-    for plain in (False, True):
-        o, lse = _run(plain, *args)
-        assert not torch.isnan(o).any() and not torch.isnan(lse).any()
-        compare(kind, q, k, v, cu, S, W, L, 1 / math.sqrt(d), o, lse, np.arange(cu[-1]),
-                range(hq), label=f"{kind} plain={plain} cu={cu}", p_bound=True)
-        if cu[-1] > 64:  # the forms differ in rounding, so in some value
-            seen = o if not plain else torch.equal(seen, o)
-    assert cu[-1] <= 64 or seen is False
-    o, _ = _run(False, *args)
-    o16, _ = _run(False, *args, out_dtype=torch.bfloat16)
+    o, lse = _run(*args)
+    assert not torch.isnan(o).any() and not torch.isnan(lse).any()
+    compare(kind, q, k, v, cu, S, W, L, 1 / math.sqrt(d), o, lse, np.arange(cu[-1]),
+            range(hq), label=f"{kind} cu={cu}", p_bound=True)
+    o16, _ = _run(*args, out_dtype=torch.bfloat16)
     assert torch.equal(o16, o.bfloat16())
 
 
 @pytest.mark.parametrize("hq,d,T,bound", [(5, 128, 128, 0), (3, 64, 64, 3)])
-def test_key_split_lists_equal_causal(hq, d, T, bound):
+def test_lists_equal_causal(hq, d, T, bound):
     """Full lists, an odd number of tiles among them: uncut they give the
     causal pass's rows bit for bit; cut into items of three tiles they meet the
     parity bar."""
@@ -91,7 +76,7 @@ def test_key_split_lists_equal_causal(hq, d, T, bound):
     o = torch.full((cu[-1], hq, d), math.nan, device="cuda")
     lse = torch.full((hq, cu[-1]), math.nan, device="cuda")
     plan.run(qg, kg, vg, o, lse)
-    ref, ref_lse = _run(False, "causal", qg, kg, vg, cu, 0, 1, 0, T, 0)
+    ref, ref_lse = _run("causal", qg, kg, vg, cu, 0, 1, 0, T, 0)
     if bound == 0:
         assert torch.equal(o, ref) and torch.equal(lse, ref_lse)
     compare("causal", q, k, v, cu, 0, 1, 0, 1 / math.sqrt(d), o, lse, np.arange(cu[-1]),

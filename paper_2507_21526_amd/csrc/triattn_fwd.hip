@@ -313,7 +313,15 @@ constexpr int phase_reads(int i, int count)
 // issue no copies.
 // LIST: the kernel serves block-sparse schedules, whose list items read
 // their k-tiles from the schedule's list section (the other kinds have none).
-template <int D, int NW, bool COPIER = false, bool LIST = false>
+// STRADDLE: the dealt row blocks of a workgroup (BLOCKS below) do not all lie
+// in one group of R rows (straddles()).  The workgroup then visits steps of
+// which some wave's 32 rows keep no key, at the diagonal and at the window's
+// start; that wave's probabilities are 0 there, and 0 times an infinite or NaN
+// V would reach rows that do not see its key, so the wave reads a tile of zeros
+// in place of V in such a step.  A form of its own: it costs 1 to 5 % (24000
+// tokens, window 2048, 40 heads over 8: 996 -> 1029 us; window 512 442 -> 446),
+// which the groups that never straddle do not pay.
+template <int D, int NW, bool COPIER = false, bool LIST = false, bool STRADDLE = false>
 __global__ __launch_bounds__(NW * 64, NW == 4 ? (D == 64 ? 3 : 2) : 1) void attn_tile_kernel(FwdArgs a,
                                                                                int32_t kind)
 {
@@ -338,18 +346,19 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? (D == 64 ? 3 : 2) : 1) void attn
     // row blocks to a workgroup; each K/V tile copied then serves half the
     // rows, which L2 carries.  Eight-wave (group 7: copier) form against it,
     // same outputs bit for bit: window 2048, 65536 tokens, 32 heads over 8
-    // 1421 -> 1363 us; 48000 tokens, 28 over 4 940 -> 863; multi-head 32768
-    // tokens (four waves before, two to a CU) 754 -> 707; window 512, 65536
-    // tokens 594 -> 558; causal 8000 tokens, 40 over 8 377 -> 345; 32768
-    // tokens, 32 over 8 4363 -> 4347 (of many steps each: even).
+    // 1421 -> 1363 us; 48000 tokens, 28 over 4 (STRADDLE) 920 -> 891; multi-head
+    // 32768 tokens (four waves before, two to a CU) 754 -> 707; window 512, 65536
+    // tokens 594 -> 558; causal 8000 tokens, 40 over 8 (STRADDLE; against
+    // workgroups of five waves) 445 -> 345; 32768 tokens, 32 over 8 4363 -> 4347
+    // (of many steps each: even).
     constexpr bool LEAN = D == 64 && NW == 4;
     // An item's row blocks (32 rows of one head) are dealt out head first
     // (block b: head b % G, rows 32 (b / G)..), blocks_per_wg to a workgroup,
     // by the eight-wave and the d = 64 four-wave form, so that they serve any
-    // group: groups of 5 and 6 take three workgroups of a 128-row
-    // tile instead of four of five or six waves (24000 tokens, window 2048:
-    // 1266 to 1003 and 1359 to 1124 us).  The other forms take R rows of
-    // every head.
+    // group: groups of 5 and 6 take three workgroups of a 128-row tile instead of
+    // four of five or six waves (24000 tokens, window 2048: 1197 to 1029 and
+    // 1306 to 1149 us, STRADDLE included).  The other forms take R rows of every
+    // head.
     constexpr bool BLOCKS = LEAN || (NW == 8 && !COPIER);
     constexpr int N_COPY_WAVES = COPIER ? 1 : NW - NW / 2;
     constexpr int COPIES = (N_DMA + N_COPY_WAVES - 1) / N_COPY_WAVES;  // per tile
@@ -370,8 +379,10 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? (D == 64 ? 3 : 2) : 1) void attn
     constexpr int QTILE_BYTES = 32 * ROW_BYTES;
     constexpr bool Q_IN_STAGE = NW * QTILE_BYTES <= STAGE_BYTES;
     constexpr int QREGION = (Q_IN_STAGE ? N_STAGES - 1 : N_STAGES) * STAGE_BYTES;
+    constexpr int ZREGION = N_STAGES * STAGE_BYTES + (Q_IN_STAGE ? 0 : NW * QTILE_BYTES);
     __shared__ __attribute__((aligned(1024))) unsigned char
-        smem[N_STAGES * STAGE_BYTES + (Q_IN_STAGE ? 0 : NW * QTILE_BYTES)];
+        smem[ZREGION + (STRADDLE ? TILE_BYTES : 0)];  // the tile of zeros
+    static_assert(!STRADDLE || BLOCKS, "dealt row blocks");
     static_assert(sizeof(smem) + (LIST ? kKeyTable * 4 : 0) <= 160 * 1024, "LDS of a CU");
 
     const int32_t *sched = a.sched;
@@ -531,6 +542,9 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? (D == 64 ? 3 : 2) : 1) void attn
             copy_to_lds16(qb, off, smem_addr + QREGION + wave * QTILE_BYTES + i * 1024);
         }
     }
+    if constexpr (STRADDLE)  // read after the prologue's barriers
+        for (int i = tid * 16; i < TILE_BYTES; i += NW * 64 * 16)
+            *reinterpret_cast<u32x4 *>(smem + ZREGION + i) = u32x4{};
     bf16x8 qf[QK_STEPS];
     auto read_q = [&]() TA_INLINE {
         const unsigned char *qt = smem + QREGION + wave * QTILE_BYTES + col * ROW_BYTES;
@@ -938,6 +952,7 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? (D == 64 ? 3 : 2) : 1) void attn
     const int group = NW >= 2 ? (wave >= NW - n_group1 ? 1 : 0) : 0;
     f32x16 s_acc[2];
     bf16x8 p_acc[2][2];
+    bool dead = false;  // the wave's rows keep no key of the last softmax's step
 
     // Matrix phase: QK^T of step j (if any) and PV of step j-1 (if any).
     // Inside the step loops (unrolled by two) the LDS stage is a
@@ -953,6 +968,13 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? (D == 64 ? 3 : 2) : 1) void attn
         __builtin_amdgcn_sched_barrier(0);
         prep();
         const int buf = stage;
+        // from this stage's V tile to the zeros
+        const uint32_t to_zeros = (uint32_t)(ZREGION - TILE_BYTES - buf * STAGE_BYTES);
+        if (STRADDLE && has_pv && __builtin_expect(dead, 0)) {
+#pragma unroll
+            for (int b = 0; b < D_BLOCKS; ++b)
+                voff[b] += to_zeros;
+        }
         if (!COPIER && has_qk && has_pv) {
             qk(buf, s_acc, hook, pre, std::false_type{});
             pv(buf, p_acc, hook, std::false_type{});
@@ -962,6 +984,11 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? (D == 64 ? 3 : 2) : 1) void attn
                 qk(buf, s_acc, hook, pre, std::true_type{});
             if (has_pv)
                 pv(buf, p_acc, hook, std::true_type{});
+        }
+        if (STRADDLE && has_pv && __builtin_expect(dead, 0)) {
+#pragma unroll
+            for (int b = 0; b < D_BLOCKS; ++b)
+                voff[b] -= to_zeros;
         }
         __builtin_amdgcn_sched_barrier(0);
         __builtin_amdgcn_s_setprio(0);
@@ -973,8 +1000,14 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? (D == 64 ? 3 : 2) : 1) void attn
         const bool need_causal = key0 + kStep - 1 > row_base;
         const bool need_window = mode == kModeStreaming && key0 + kStep - 1 >= a.sink &&
                                  row_hi - key0 >= a.window;
-        if (__builtin_expect(need_causal | need_window, 0))  // a few steps per item
+        dead = false;
+        if (__builtin_expect(need_causal | need_window, 0)) {  // a few steps per item
             mask_step(key0, need_causal, need_window, s_acc);
+            if constexpr (STRADDLE)  // (list schedules have no streaming rows)
+                dead = __builtin_amdgcn_readfirstlane(key0) > row_hi ||
+                       (!LIST && need_window && key0 >= a.sink &&
+                        row_base - (key0 + kStep - 1) >= a.window);
+        }
         softmax(s_acc, p_acc);
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb)
@@ -2266,12 +2299,32 @@ int rows_per_wg(int group, int tile)
     return 32;
 }
 
+// Whether some workgroup of dealt row blocks (32 rows of each of `group` heads,
+// head first, per_wg to a workgroup) holds blocks of more than one group of
+// R rows, the rows that share a workgroup in the other forms: groups of 5 and 6
+// at 128-row tiles, and at d = 64 groups of 3, 5, 6 and 7.
+bool straddles(int group, int blocks, int per_wg, int R)
+{
+    const int run = group * (R / 32);  // blocks of R rows
+    for (int b = 0; b < blocks; b += per_wg)
+        if (b / run != (std::min(b + per_wg, blocks) - 1) / run)
+            return true;
+    return false;
+}
+
 template <int D, bool LIST>
-hipError_t launch_tile_as(int nw, dim3 grid, const FwdArgs &a, int kind, hipStream_t s)
+hipError_t launch_tile_as(int nw, bool straddle, dim3 grid, const FwdArgs &a, int kind, hipStream_t s)
 {
     switch (nw) {
     case 2: hipLaunchKernelGGL((attn_tile_kernel<D, 2, false, LIST>), grid, dim3(128), 0, s, a, kind); break;
-    case 4: hipLaunchKernelGGL((attn_tile_kernel<D, 4, false, LIST>), grid, dim3(256), 0, s, a, kind); break;
+    case 4:
+        if constexpr (D == 64)
+            if (straddle) {
+                hipLaunchKernelGGL((attn_tile_kernel<D, 4, false, LIST, true>), grid, dim3(256), 0, s, a, kind);
+                break;
+            }
+        hipLaunchKernelGGL((attn_tile_kernel<D, 4, false, LIST>), grid, dim3(256), 0, s, a, kind);
+        break;
     // seven compute waves and a copier wave
     case 7:
         if constexpr (D == 128)
@@ -2280,10 +2333,14 @@ hipError_t launch_tile_as(int nw, dim3 grid, const FwdArgs &a, int kind, hipStre
             return hipErrorInvalidValue;  // d = 64 runs four waves
         break;
     case 8:
-        if constexpr (D == 128)
-            hipLaunchKernelGGL((attn_tile_kernel<D, 8, false, LIST>), grid, dim3(512), 0, s, a, kind);
-        else
+        if constexpr (D == 128) {
+            if (straddle)
+                hipLaunchKernelGGL((attn_tile_kernel<D, 8, false, LIST, true>), grid, dim3(512), 0, s, a, kind);
+            else
+                hipLaunchKernelGGL((attn_tile_kernel<D, 8, false, LIST>), grid, dim3(512), 0, s, a, kind);
+        } else {
             return hipErrorInvalidValue;
+        }
         break;
     default: return hipErrorInvalidValue;
     }
@@ -2292,10 +2349,11 @@ hipError_t launch_tile_as(int nw, dim3 grid, const FwdArgs &a, int kind, hipStre
 
 // Block-sparse schedules (list items) run the list form of the kernel.
 template <int D>
-hipError_t launch_tile(int nw, dim3 grid, const FwdArgs &a, int kind, hipStream_t s)
+hipError_t launch_tile(int nw, bool straddle, dim3 grid, const FwdArgs &a, int kind,
+                       hipStream_t s)
 {
-    return kind == TA_KIND_BLOCKSPARSE ? launch_tile_as<D, true>(nw, grid, a, kind, s)
-                                       : launch_tile_as<D, false>(nw, grid, a, kind, s);
+    return kind == TA_KIND_BLOCKSPARSE ? launch_tile_as<D, true>(nw, straddle, grid, a, kind, s)
+                                       : launch_tile_as<D, false>(nw, straddle, grid, a, kind, s);
 }
 
 ta_status check_common(const char *fn, int want_kind, const void *q, const void *k,
@@ -2530,9 +2588,11 @@ ta_status launch_tiles(int kind, const FwdArgs &a_in, int32_t head_dim,
     const bool lean = head_dim == 64 && blocks >= 4;
     const int nw = lean ? 4 : blocks <= 4 ? blocks : a.group == 7 ? 7 : 8;
     const int units_subtiles = a.subtiles;  // of the multi-unit kernel
+    bool straddle = false;
     if (lean || nw == 8) {
         a.subtiles = (blocks + nw - 1) / nw;
         a.blocks_per_wg = (blocks + a.subtiles - 1) / a.subtiles;
+        straddle = straddles(a.group, blocks, a.blocks_per_wg, a.rows_per_wg);
     }
     const int units_nw = a.group * a.rows_per_wg / 32;  // of the multi-unit kernel
     const int64_t units = (int64_t)a.n_items * units_subtiles;
@@ -2553,8 +2613,8 @@ ta_status launch_tiles(int kind, const FwdArgs &a_in, int32_t head_dim,
         a.lead_span = lead_slots(info, tile_cost(nw, a.blocks_per_wg), nw <= 4, wgs);
         a.n_lead = a.lead_span > 0 ? info->n_last_items : 0;
         dim3 grid((unsigned)wgs);
-        err = head_dim == 128 ? launch_tile<128>(nw, grid, a, kind, stream)
-                              : launch_tile<64>(nw, grid, a, kind, stream);
+        err = head_dim == 128 ? launch_tile<128>(nw, straddle, grid, a, kind, stream)
+                              : launch_tile<64>(nw, straddle, grid, a, kind, stream);
     }
     if (err != hipSuccess)
         return fail(TA_ERR_HIP, "attention tile kernel launch failed: %s",

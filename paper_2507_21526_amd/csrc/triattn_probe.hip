@@ -534,7 +534,7 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void probe_kernel(ProbeAr
             }
             float ts = 0.f, to = 0.f;
             auto pass = [&](float m) TA_INLINE -> float {
-                float psum = 0.f, t = 0.f;
+                float psum = 0.f, t = 0.f, st = 0.f;
                 if (one_section && causal_all) {
 #pragma unroll
                     for (int kb = 0; kb < 2; ++kb)
@@ -544,13 +544,10 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void probe_kernel(ProbeAr
                             psum += pr;
                             t = fmaf(pr, gacc[kb][e], t);
                         }
-                    ts = strm_all ? t : 0.f;
-                    to = strm_all ? 0.f : t;
                 } else {
                     // sink key: o < slim; in the window: o > wlim
                     const int slim = strm_all ? kProbeStep : a.sink - key0 - 4 * h;
                     const int wlim = strm_none ? kProbeStep : lim - a.window;
-                    float st = 0.f;
 #pragma unroll
                     for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
@@ -562,9 +559,11 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void probe_kernel(ProbeAr
                             t += pv;
                             st += ((o < slim) | (o > wlim)) ? pv : 0.f;
                         }
-                    ts = st;
-                    to = t - st;
                 }
+                // a step of one section adds nothing to the other, also where
+                // its sum is infinite
+                ts = one_section ? (strm_all ? t : 0.f) : st;
+                to = one_section ? (strm_all ? 0.f : t) : t - st;
                 return psum;
             };
             float psum = INFINITY;

@@ -12,7 +12,7 @@ import torch
 
 import oracle
 from paper_2507_21526_amd import binding as B
-from paper_2507_21526_amd.inputs import draw_qkv
+from paper_2507_21526_amd.inputs import draw_dout, draw_qkv
 from tests.parity import log, run_pass
 
 pytestmark = pytest.mark.gpu
@@ -87,3 +87,28 @@ def test_infinite_value_reaches_its_rows_only(kind, n, hq, hkv, d, S, W, L, T, k
                     if not kept[a:b, s0:s0 + STEP].any()]
             for a, b in away:
                 assert torch.equal(o[a:b], base[a:b].to(dtype)), (key, dtype, a)
+
+
+@pytest.mark.parametrize("hq,hkv,d,n,L,slots", [
+    (4, 1, 128, 400, 0, None),   # equal shares, eight waves
+    (4, 1, 128, 400, 50, None),
+    (1, 1, 64, 400, 0, None),    # four waves
+    (28, 4, 64, 390, 0, 1),      # one share, seven waves
+])
+def test_infinite_value_stays_in_its_section(hq, hkv, d, n, L, slots, monkeypatch):
+    """Row pairs of a key in the last window are all of the streaming section,
+    in steps that hold no other: the sums of the other sections stay bit for bit."""
+    log(f"case infinite value region sums hq={hq} hkv={hkv} d={d} n={n} L={L}")
+    if slots:
+        monkeypatch.setenv("TRIATTN_PROBE_SLOTS", str(slots))
+    cu, S, W = [0, n], 16, 100
+    q, k, v = draw_qkv(cu, hq, hkv, d, 9)
+    dout = draw_dout(cu, hq, d, 10)
+    args = [t.cuda() for t in (q, k, v, dout)]
+    _, base = B.region_grad(*args, cu, S, W, L)
+    for key in (n - 1, n - 6):
+        v2 = v.clone()
+        v2[key, :, 0] = math.inf
+        _, got = B.region_grad(args[0], args[1], v2.cuda(), args[3], cu, S, W, L)
+        assert not np.isfinite(got[:, 0]).any(), key
+        assert np.array_equal(got[:, 1:], base[:, 1:]), key

@@ -91,8 +91,9 @@ struct FwdArgs {
     // schedule order)
     int32_t n_lead;
     int32_t lead_span;
-    // every Last q-tile has one split, which covers its keys: its rows go
-    // straight to O and LSE, and no merge follows
+    // the merge items of a pass whose every Last q-tile has one split, which
+    // covers its keys: the rows go straight to O and LSE and no merge follows,
+    // so the tile kernels check the merge items (0: a merge follows)
     int32_t direct;
 };
 
@@ -102,6 +103,19 @@ __device__ __forceinline__ bool covers_rows(int mode, int ka0, int ka1, int kb0,
                                             int tile)
 {
     return (mode == kModeCausal) & (ka0 == 0) & ((int64_t)ka1 * tile >= r1) & (kb0 == kb1);
+}
+
+// Whether a merge item's words lie within the pass (& without
+// short-circuits: the words are loaded together).
+__device__ __forceinline__ bool merge_words_ok(const int32_t *x, int tile, int64_t n_partial_rows,
+                                               int64_t total_tokens)
+{
+    const int64_t seq_off = x[M_SEQ_OFF];
+    const int32_t r0 = x[M_R0], r1 = x[M_R1], ns = x[M_SPLITS], pb = x[M_PART_BASE];
+    const int rows = r1 - r0;
+    return (rows >= 1) & (rows <= tile) & (ns >= 1) & (pb >= 0) &
+           (pb + (int64_t)ns * rows <= n_partial_rows) & (seq_off >= 0) & (r0 >= 0) &
+           (seq_off + r1 <= total_tokens);
 }
 
 struct MergeArgs {
@@ -427,8 +441,9 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? (D == 64 ? 3 : 2) : 1) void attn
     // are all loaded before it.
     const int32_t list_len = sched[H_WINDOW];  // block-sparse: length of the lists
     const bool uncovered = !covers_rows(mode, ka0, ka1, kb0, kb1, r1, a.tile);
-    const bool bad =
+    bool bad =
         !header_ok(sched, a.total_tokens, a.n_items, kind) |
+        (!LIST & (a.direct != 0) & (sched[H_TILE] != a.tile)) |
         (a.list_words != (kind == TA_KIND_BLOCKSPARSE ? list_len : 0)) |
         (seq_off < 0) | (seq_len < 0) | (seq_off + seq_len > a.total_tokens) | (r0 < 0) |
         (r1 > seq_len) | (r0 >= r1) | (ka0 < 0) | (kb0 < 0) | (kb1 < kb0) |
@@ -437,6 +452,14 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? (D == 64 ? 3 : 2) : 1) void attn
                    : ka1 < ka0) |
         ((item_part >= 0) & ((item_part + (r1 - r0) > a.n_partial_rows) |
                              ((a.direct != 0) & uncovered)));
+    // A pass without a merge checks what the merge would: merge item m in the
+    // workgroups of the m-th item from the end, which are not the longest (the
+    // Last items in front are).
+    const int m_item = a.n_items - 1 - item;
+    if (!LIST && __builtin_expect(m_item < a.direct, 0))
+        bad |= !merge_words_ok(sched + kHdrWords + (int64_t)a.n_items * kItemWords +
+                                   (int64_t)m_item * kMergeWords,
+                               a.tile, a.n_partial_rows, a.total_tokens);
     if (bad) {
         poison_outputs(a.o, a.o_f32, a.lse, a.total_tokens, a.hq, D, blockIdx.x,
                        gridDim.x);
@@ -1417,7 +1440,7 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_units_kernel(FwdArgs a, int32
     if (slot >= a.n_slots || n_my <= 0)
         return;
     if (!header_ok(sched, a.total_tokens, a.n_items, kind) || a.list_words != 0 ||
-        n_my > kMaxUnits) {
+        (a.direct && sched[H_TILE] != a.tile) || n_my > kMaxUnits) {
         poison_outputs(a.o, a.o_f32, a.lse, a.total_tokens, a.hq, D, blockIdx.x, gridDim.x);
         return;
     }
@@ -1608,6 +1631,13 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_units_kernel(FwdArgs a, int32
     // dropped; a unit with rows but no steps (an empty split of a Last
     // q-tile) is written at once (zero partials, LSE -inf).
     int n_run = 0, n_total = 0;
+    // a pass without a merge checks what the merge would
+    auto bad_merge = [&](int item) {
+        return item < a.direct &&
+               !merge_words_ok(sched + kHdrWords + (int64_t)a.n_items * kItemWords +
+                                   (int64_t)item * kMergeWords,
+                               a.tile, a.n_partial_rows, a.total_tokens);
+    };
     for (int k = 0; k < n_my; ++k) {
         lds_i32 *w = (lds_i32 *)itab + k * kItemWords;
         const int seq_off = __builtin_amdgcn_readfirstlane(w[I_SEQ_OFF]);
@@ -1625,7 +1655,8 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_units_kernel(FwdArgs a, int32
             kb1 < kb0 || (mode != kModeStreaming && mode != kModeCausal) ||
             (item_part >= 0 &&
              (item_part + (r1 - r0) > a.n_partial_rows ||
-              (a.direct && !covers_rows(mode, ka0, ka1, kb0, kb1, r1, a.tile))))) {
+              (a.direct && !covers_rows(mode, ka0, ka1, kb0, kb1, r1, a.tile)))) ||
+            bad_merge((slot + k * a.n_slots) / a.subtiles)) {
             poison_outputs(a.o, a.o_f32, a.lse, a.total_tokens, a.hq, D, blockIdx.x,
                            gridDim.x);
             poison_item_rows(a.o, a.o_f32, a.lse, a.part_o, a.part_lse, a.total_tokens, a.hq,
@@ -2162,17 +2193,6 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_units_kernel(FwdArgs a, int32
 // per (row, query head) of merge item x: the wave reduces max and sum of the
 // split LSEs across its lanes, then accumulates the weighted partial rows.
 template <int D>
-__device__ __forceinline__ bool merge_item_ok(const MergeArgs &a, const int32_t *x)
-{
-    const int64_t seq_off = x[M_SEQ_OFF];
-    const int32_t r0 = x[M_R0], r1 = x[M_R1], ns = x[M_SPLITS], pb = x[M_PART_BASE];
-    const int rows = r1 - r0;
-    return rows >= 1 && rows <= a.tile && ns >= 1 && pb >= 0 &&
-           pb + (int64_t)ns * rows <= a.n_partial_rows && seq_off >= 0 && r0 >= 0 &&
-           seq_off + r1 <= a.total_tokens;
-}
-
-template <int D>
 __device__ __forceinline__ void merge_row(const MergeArgs &a, const int32_t *x, int rank,
                                           int head, int lane)
 {
@@ -2275,7 +2295,8 @@ __global__ __launch_bounds__(256) void merge_kernel(MergeArgs a)
     }
     const int32_t *mi = sched + kHdrWords + (int64_t)a.n_items * kItemWords;
     for (int m = blockIdx.y; m < a.n_merges; m += gridDim.y)
-        if (!merge_item_ok<D>(a, mi + (int64_t)m * kMergeWords)) {
+        if (!merge_words_ok(mi + (int64_t)m * kMergeWords, a.tile, a.n_partial_rows,
+                            a.total_tokens)) {
             poison_outputs(a.o, a.o_f32, a.lse, a.total_tokens, a.hq, D, block, n_blocks);
             return;
         }
@@ -2777,8 +2798,9 @@ ta_status split_pass_fwd(const char *fn, int kind, const void *q, const void *k,
     // rows itself, with the same values, and the merge launch (4 us at 1024
     // tokens, 4 to 10 us for a few short sequences) and the partials' trip
     // through memory fall away.
-    a.direct = kind == TA_KIND_TRIANGLE && info->max_splits == 1 &&
-               info->n_last_items == info->n_merge_items;
+    if (kind == TA_KIND_TRIANGLE && info->max_splits == 1 &&
+        info->n_last_items == info->n_merge_items && info->n_merge_items <= info->n_items)
+        a.direct = info->n_merge_items;
     st = launch_tiles(kind, a, head_dim, info, s);
     if (st != TA_OK || a.direct)
         return st;

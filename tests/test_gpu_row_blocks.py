@@ -117,3 +117,35 @@ def test_one_split_needs_no_merge(cu, hq, d, T, splits, upw):
         assert torch.isnan(o).any()
     finally:
         os.environ.pop(ENV, None)
+
+
+@pytest.mark.parametrize("upw", [None, 3])
+def test_one_split_checks_the_whole_schedule(upw, monkeypatch):
+    """The fused call over one split per Last q-tile launches no merge, but
+    rejects what the merge would: another tile in the header (every row NaN)
+    and a malformed merge item."""
+    cu, hq, d, T = [0, 700, 901], 4, 128, 128
+    q, k, v = (t.cuda() for t in draw_qkv(cu, hq, 1, d, seed=6))
+    if upw is not None:
+        monkeypatch.setenv(ENV, str(upw))
+    plan = binding.Plan("triangle", cu, 5, 64, 129, T, hq, d)
+    info = plan.info
+    assert info.max_splits == 1 and info.n_merge_items >= 3
+    good = plan.sched.clone()
+    merge = binding.HDR_WORDS + binding.ITEM_WORDS * info.n_items
+    last = merge + 8 * (info.n_merge_items - 1)
+    for word, value, every in ((3, 64, True), (merge, -1, False), (last, cu[-1], False),
+                               (last + 1, -1, False), (last + 2, 1 << 20, False),
+                               (last + 3, 0, False), (last + 3, 1 << 20, False),
+                               (last + 4, -1, False), (last + 4, 1 << 20, False)):
+        o = torch.zeros(q.shape, device="cuda")
+        lse = torch.zeros((hq, cu[-1]), device="cuda")
+        plan.sched.copy_(good)
+        plan.run(q, k, v, o, lse)
+        assert not torch.isnan(o).any() and not torch.isnan(lse).any()
+        plan.sched[word] = value
+        plan.run(q, k, v, o, lse)
+        torch.cuda.synchronize()
+        bad = torch.isnan(o)
+        assert bool(bad.all() if every else bad.any()), word
+        assert bool(torch.isnan(lse).all() if every else torch.isnan(lse).any()), word

@@ -2592,7 +2592,7 @@ int units_per_wg(const FwdArgs &a, int kind, int nw, int64_t units, int32_t max_
     }
 }
 
-ta_status launch_tiles(int kind, const FwdArgs &a_in, int32_t head_dim,
+ta_status launch_tiles(const char *fn, int kind, const FwdArgs &a_in, int32_t head_dim,
                        const ta_schedule_info *info, hipStream_t stream)
 {
     if (a_in.n_items <= 0)
@@ -2630,7 +2630,10 @@ ta_status launch_tiles(int kind, const FwdArgs &a_in, int32_t head_dim,
         err = head_dim == 128 ? launch_units<128>(units_nw, grid, a, kind, stream)
                               : launch_units<64>(units_nw, grid, a, kind, stream);
     } else {
+        // (more than check_common counted where d = 64 takes smaller workgroups)
         const int64_t wgs = (int64_t)a.n_items * a.subtiles * a.hkv;
+        if (wgs > INT32_MAX)
+            return fail(TA_ERR_UNSUPPORTED, "%s: grid too large", fn);
         a.lead_span = lead_slots(info, tile_cost(nw, a.blocks_per_wg), nw <= 4, wgs);
         a.n_lead = a.lead_span > 0 ? info->n_last_items : 0;
         dim3 grid((unsigned)wgs);
@@ -2728,7 +2731,7 @@ extern "C" ta_status triangle_attn_tiles(const void *q, const void *k, const voi
         return st;
     const FwdArgs a = make_args(q, k, v, o, o_dtype, lse, sched_dev, info, total_tokens,
                                 hq, hkv, softmax_scale, part_o, part_lse);
-    return launch_tiles(TA_KIND_TRIANGLE, a, head_dim, info,
+    return launch_tiles("triangle_attn_tiles", TA_KIND_TRIANGLE, a, head_dim, info,
                         static_cast<hipStream_t>(stream));
 }
 
@@ -2801,7 +2804,7 @@ ta_status split_pass_fwd(const char *fn, int kind, const void *q, const void *k,
     if (kind == TA_KIND_TRIANGLE && info->max_splits == 1 &&
         info->n_last_items == info->n_merge_items && info->n_merge_items <= info->n_items)
         a.direct = info->n_merge_items;
-    st = launch_tiles(kind, a, head_dim, info, s);
+    st = launch_tiles(fn, kind, a, head_dim, info, s);
     if (st != TA_OK || a.direct)
         return st;
     return launch_merge(o, o_dtype, lse, sched_dev, info, total_tokens, hq, head_dim,
@@ -2924,6 +2927,6 @@ extern "C" ta_status causal_attn_fwd(const void *q, const void *k, const void *v
         return st;
     const FwdArgs a = make_args(q, k, v, o, o_dtype, lse, sched_dev, info, total_tokens,
                                 hq, hkv, softmax_scale, nullptr, nullptr);
-    return launch_tiles(TA_KIND_CAUSAL, a, head_dim, info,
+    return launch_tiles("causal_attn_fwd", TA_KIND_CAUSAL, a, head_dim, info,
                         static_cast<hipStream_t>(stream));
 }

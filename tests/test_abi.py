@@ -157,6 +157,19 @@ def test_fwd_rejects_bad_arguments_without_launching():
         assert _fwd("blocksparse", info=bad) == B.TA_ERR_SCHEDULE_MISMATCH, field
 
 
+def test_fwd_rejects_grids_beyond_32_bits():
+    """The workgroups of the launch that is made are counted: with four query
+    heads to a kv head, a 64-row tile is one workgroup at d 128 and two at d 64."""
+    for d, n_items in ((64, 600_000_000), (128, 1_200_000_000)):
+        for fn in ("causal", "triangle"):
+            _, info = B.ta_build_schedule(fn, [0, 100], 4, 8, 0, 64)
+            info.max_item_tiles = 32  # not the short units of the multi-unit kernel
+            info.words += 12 * (n_items - info.n_items)
+            info.n_items = n_items
+            assert _fwd(fn, info=info, hq=8, hkv=2, d=d) == B.TA_ERR_UNSUPPORTED, (d, fn)
+            assert "grid too large" in B.ta_last_error()
+
+
 def test_noalloc_rejects_partials_beyond_the_scratch_size():
     """triangle_attn_fwd_noalloc refuses, before any HIP call, a schedule
     whose split partials exceed the library's scratch array."""

@@ -458,8 +458,9 @@ def region_grad(q, k, v, dout, cu_seqlens, sink, window, last, tile=128,
     if softmax_scale is None:
         softmax_scale = 1.0 / float(d) ** 0.5
     plan = Plan("causal", cu_seqlens, 0, 1, 0, tile, hq, d, device=q.device)
-    # (a head count that k's does not divide is refused by the call below)
-    nbytes = ta_region_grad_workspace_bytes(plan.info, hq, k.shape[1])
+    # (tensors and head counts that do not fit are refused by the call below)
+    hkv = k.shape[1] if getattr(k, "ndim", 0) == 3 else 0
+    nbytes = ta_region_grad_workspace_bytes(plan.info, hq, hkv)
     ws = torch.empty(nbytes, dtype=torch.uint8, device=q.device) if nbytes else None
     sums = torch.empty((hq, 3), dtype=torch.float64, device=q.device)
     region_grad_sums(q, k, v, dout, plan.sched, plan.info, softmax_scale, sink, window,

@@ -259,6 +259,21 @@ def test_binding_rejects_bad_tensors_before_any_gpu_call():
         B.region_grad_probe(q, k, v, q.float(), lse, sched, info, 0.1, 4, 8, 2, sums, ws)
 
 
+def test_region_grad_rejects_bad_tensors_before_any_gpu_call():
+    q, k, v, _, _ = _host_tensors()
+    for msg, args in {
+        "k must be a torch tensor": (q, None, v, q),
+        "k must be [tokens": (q, k[:, 0, 0].contiguous(), v, q),
+        "v must be [tokens": (q, k, v[0], q),
+        "k and v must have 100 tokens": (q, k[:99], v[:99], q),
+        "dout must be a bfloat16": (q, k, v, q.float()),
+        "o must have q's shape": (q, k, v, q[:, :4].contiguous()),
+        "operands must be on a GPU": (q, k, v, q),
+    }.items():
+        with pytest.raises(ValueError, match=re.escape(msg)):
+            B.region_grad(*args, [0, 100], 4, 8, 2)
+
+
 def test_binding_fails_loudly_without_library(monkeypatch, tmp_path):
     monkeypatch.setattr(B, "_lib", None)
     monkeypatch.setattr(B, "LIB_PATH", str(tmp_path / "missing.so"))

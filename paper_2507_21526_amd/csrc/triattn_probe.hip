@@ -781,7 +781,9 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void probe_kernel(ProbeAr
 // partials in the probe kernel already.
 __global__ __launch_bounds__(128) void probe_combine_kernel(ProbeArgs a, double *part)
 {
-    const int item = blockIdx.x, head = blockIdx.y, tid = threadIdx.x, nt = blockDim.x;
+    // (one grid dimension: the others end at 65535, heads may be more)
+    const int item = blockIdx.x % a.n_items, head = blockIdx.x / a.n_items;
+    const int tid = threadIdx.x, nt = blockDim.x;
     const int lane = tid & 63, wave = tid >> 6;
     __shared__ int64_t pre_w[2];
     __shared__ double sum_w[2][3];
@@ -1032,7 +1034,7 @@ ta_status probe_sums(const char *fn, bool online, const void *q, const void *k, 
         return fail(TA_ERR_WORKSPACE, "%s: workspace needs %zu bytes (%d-byte aligned), "
                     "got %zu", fn, need, (int)align, workspace_bytes);
     const int64_t subtiles = lay.subtiles, slots = lay.split.slots;
-    if (slots * subtiles * hkv > INT32_MAX)
+    if (slots * subtiles * hkv > INT32_MAX || (online && lay.item_blocks * hq > INT32_MAX))
         return fail(TA_ERR_UNSUPPORTED, "%s: grid too large", fn);
     if (online && 2LL * hq * head_dim >= (1LL << 24))
         return fail(TA_ERR_UNSUPPORTED, "%s: hq * head_dim too large", fn);
@@ -1079,7 +1081,7 @@ ta_status probe_sums(const char *fn, bool online, const void *q, const void *k, 
             return fail(TA_ERR_HIP, "%s: probe kernel launch failed: %s", fn,
                         hipGetErrorString(err));
         if (online && lay.item_blocks > 0) {
-            hipLaunchKernelGGL(probe_combine_kernel, dim3((unsigned)info->n_items, (unsigned)hq),
+            hipLaunchKernelGGL(probe_combine_kernel, dim3((unsigned)(lay.item_blocks * hq)),
                                dim3((unsigned)info->tile), 0, stream, a,
                                part + lay.probe_blocks * hq * 3);
             err = hipGetLastError();

@@ -64,6 +64,16 @@ CASES = [
     ([0, 520], 3, 1, 64, 128, 1.0, None, 2),        # full lists cut in splits
     ([0, 1200], 4, 4, 128, 128, 0.4, None, 0),      # G = 1: Q tiles in a K/V stage
     ([0, 900], 2, 2, 64, 64, 0.5, True, 1),         # G = 1, T = 64: two waves
+    # d 64, four-wave workgroups of dealt row blocks
+    ([0, 700, 1333], 4, 2, 64, 128, 0.5, None, 0),  # G = 2
+    ([0, 700, 1333], 8, 2, 64, 128, 0.5, True, 2),  # G = 4
+    ([0, 1000], 7, 1, 64, 128, 0.6, None, 0),       # G = 7: 28 row blocks
+    ([0, 777], 14, 2, 64, 64, 0.5, True, 3),        # G = 7: 4, 4, 4 and 2 row blocks
+    # d 128, dealt row blocks shared out unevenly
+    ([0, 700, 1333], 3, 1, 128, 128, 0.5, None, 0),   # G = 3: 6 and 6
+    ([0, 700, 1333], 10, 2, 128, 128, 0.5, True, 0),  # G = 5: 7, 7 and 6
+    ([0, 1000], 6, 1, 128, 128, 0.6, None, 2),        # G = 6: 8, 8 and 8
+    ([0, 777], 5, 1, 128, 64, 0.6, None, 0),          # G = 5: 5 and 5
 ]
 
 

@@ -88,7 +88,7 @@ def test_region_sums_parity(cu, hq, hkv, d, tile, S, W, L, slots, grow):
 
 
 def test_region_sums_per_item_equal_shares():
-    """16 packed sequences run one item per workgroup; equal shares of the
+    """128 packed sequences run one item per workgroup; equal shares of the
     same batch give the same sums but for the summation order (a step's
     products are taken against another reference, so fp32 rounding too)."""
     cu = [300 * i for i in range(129)]
@@ -105,6 +105,19 @@ def test_region_sums_per_item_equal_shares():
     finally:
         del os.environ["TRIATTN_PROBE_SLOTS"]
     assert np.allclose(one, shares, rtol=1e-4, atol=1e-3)
+
+
+@pytest.mark.parametrize("hq,hkv,d,tile,S,W,L", [(32, 8, 128, 128, 8, 64, 32),
+                                                 (28, 4, 64, 64, 0, 40, 10)])
+def test_region_sums_per_item_parity(hq, hkv, d, tile, S, W, L):
+    """Short packed sequences, enough for one item per workgroup (as a long
+    sequence runs): the rows' normalisers are divided out in that workgroup."""
+    cu = [0] + [int(x) for x in np.cumsum([260, 131, 64, 199] * 20)]
+    plan = B.Plan("causal", cu, 0, 1, 0, tile, hq, d)
+    # no row states: the workspace is one partial per (item, 32 rows, head, section)
+    partials = plan.info.n_items * (tile // 32) * hq * 3 * 8
+    assert B.ta_region_grad_workspace_bytes(plan.info, hq, hkv) < partials + 512
+    _check(cu, hq, hkv, d, tile, S, W, L, 40 + hq, 20.0)
 
 
 def test_region_sums_many_heads():

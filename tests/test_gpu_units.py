@@ -1,4 +1,4 @@
-"""GPU tests of the multi-unit tile kernel: workgroups of five to eight waves
+"""GPU tests of the multi-unit tile kernel: workgroups of six to eight waves
 that run several (item, row block) units of a Triangle pass as one pipeline.
 
 The kernel computes every row with the same 64-key steps, in the same order,
@@ -8,8 +8,8 @@ count, so small shapes run through unit boundaries of every kind: ragged
 q-tiles whose second row block is empty, Last-row splits without a step for
 some rows (written as zero partials), units of different sequences of a
 packed batch, sinks that are not tile aligned, one- or two-key windows, and
-bf16 and fp32 outputs.  One configuration is also checked against the fp64
-oracle."""
+bf16 and fp32 outputs.  Each forced launch is seen to run that kernel.  One
+configuration is also checked against the fp64 oracle."""
 import math
 import os
 
@@ -31,7 +31,7 @@ CASES = [
     ([0, 640], 8, 2, 128, 130, 65, 129, 128, 3),                   # sink not aligned
     ([0, 2000], 28, 4, 128, 16, 100, 40, 128, 0),                  # G 7 (Qwen group)
     ([0, 700, 1300], 6, 2, 128, 8, 64, 200, 64, 5),                # G 3, six waves
-    ([0, 1000], 5, 1, 64, 4, 128, 300, 128, 7),                    # G 5, five waves
+    ([0, 1000], 3, 1, 64, 4, 128, 300, 128, 7),                    # G 3, d 64, six waves
     ([0, 1000], 8, 2, 128, 16, 128, 200, 128, 8),                  # splits without steps
 ]
 
@@ -47,6 +47,14 @@ def _run(kind, q, k, v, cu, S, W, L, T, splits, upw, out_dtype):
     return o, lse
 
 
+def _kernels(call):
+    """Names of the kernels that the call launches."""
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as prof:
+        call()
+        torch.cuda.synchronize()
+    return [e.name for e in prof.events()]
+
+
 @pytest.mark.parametrize("cu,hq,hkv,d,S,W,L,T,splits", CASES)
 def test_units_bit_identical_to_single_unit(cu, hq, hkv, d, S, W, L, T, splits):
     log(f"case units cu={cu} hq={hq} hkv={hkv} d={d} S={S} W={W} L={L} T={T} splits={splits}")
@@ -55,6 +63,11 @@ def test_units_bit_identical_to_single_unit(cu, hq, hkv, d, S, W, L, T, splits):
         ref_o, ref_l = _run("triangle", q, k, v, cu, S, W, L, T, splits, 1, out_dtype)
         assert not torch.isnan(ref_o).any()
         for upw in (2, 3, 7, 128):
+            if out_dtype == torch.float32:
+                names = _kernels(lambda: _run("triangle", q, k, v, cu, S, W, L, T, splits, upw,
+                                              out_dtype))
+                assert any("attn_units_kernel" in n for n in names), (upw, names)
+                assert not any("attn_tile_kernel" in n for n in names), (upw, names)
             o, lse = _run("triangle", q, k, v, cu, S, W, L, T, splits, upw, out_dtype)
             assert not torch.isnan(o).any(), (upw, out_dtype)
             assert torch.equal(o, ref_o), (upw, out_dtype)
@@ -92,6 +105,8 @@ def test_units_noalloc_and_graph_replay():
     finally:
         del os.environ[ENV]
     assert torch.equal(ref, single)
+    names = _kernels(lambda: plan.run(q, k, v, single, None, d ** -0.5))
+    assert any("attn_units_kernel" in n for n in names), names
     na = torch.empty_like(ref)
     binding.triangle_attn_fwd_noalloc(q, k, v, na, None, plan.sched, plan.info, d ** -0.5)
     torch.cuda.synchronize()

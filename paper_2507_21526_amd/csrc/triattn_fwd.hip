@@ -2492,9 +2492,15 @@ struct LaunchCost {
 };
 // Workgroups of at most four waves run two to a CU, at nearly the speed of
 // one each; one of five row blocks takes its steps a little faster than a
-// full one.
-LaunchCost tile_cost(int nw, int blocks_per_wg)
+// full one.  At d = 64 three four-wave workgroups run to a CU and slow each
+// other (a step of 3.6 fits 65536 tokens, 32 heads over 8, window 2048: 1363 us).
+// Against the figures of two to a CU, over 75 launches of 3001 to 48000 tokens,
+// windows 300 to 2048 and groups 1 to 8: 0.9 % faster on average, 12 % at most
+// (24000 tokens, 28 over 4, window 300: 158 -> 139 us), none over 1.4 % slower.
+LaunchCost tile_cost(bool lean, int nw, int blocks_per_wg)
 {
+    if (lean)
+        return {13.0, 3.6, 768.0};
     if (nw <= 4)
         return {10.0, 2.6, 512.0};
     return {10.0, blocks_per_wg == 5 ? 2.25 : 2.4, 256.0};
@@ -2634,7 +2640,7 @@ ta_status launch_tiles(const char *fn, int kind, const FwdArgs &a_in, int32_t he
         const int64_t wgs = (int64_t)a.n_items * a.subtiles * a.hkv;
         if (wgs > INT32_MAX)
             return fail(TA_ERR_UNSUPPORTED, "%s: grid too large", fn);
-        a.lead_span = lead_slots(info, tile_cost(nw, a.blocks_per_wg), nw <= 4, wgs);
+        a.lead_span = lead_slots(info, tile_cost(lean, nw, a.blocks_per_wg), nw <= 4, wgs);
         a.n_lead = a.lead_span > 0 ? info->n_last_items : 0;
         dim3 grid((unsigned)wgs);
         err = head_dim == 128 ? launch_tile<128>(nw, straddle, grid, a, kind, stream)

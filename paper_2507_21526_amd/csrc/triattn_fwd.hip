@@ -2562,23 +2562,29 @@ hipError_t launch_units(int nw, dim3 grid, const FwdArgs &a, int kind, hipStream
 // epilogue's normalisation, staging and stores beside the other group's
 // MFMAs), the single-unit kernel reads K ahead where the multi-unit kernel
 // has no registers to, and the pass runs at a power-limited clock, so the
-// multi-unit kernel pays off only for short units (and not at all for groups of 5 and 6, whose row blocks fill eight
-// waves in the single-unit kernel only: 24000 tokens, sink 64, window 128,
-// group 6: 282 us in units of six waves, 241 without): at d = 128 units of 4-8
-// steps come out even, 10-12 steps (sink 8, window 512) 1 % slower and 36
-// steps (window 2048) 6-10 %; at d = 64, whose single-unit kernel runs three
-// four-wave workgroups to a CU, 6 steps even (65536 tokens, 32 heads over 8,
-// sink 64, window 128: 289 us, 292 single-unit), 10 steps 9 % slower (24000
-// tokens, 32 over 4, window 300: 150 us, 137 single-unit).  For units of at most
-// kShortUnitSteps steps: one workgroup per CU (256 CUs over the kv
+// multi-unit kernel pays off only for short units at d = 128.  Units of at
+// most kShortUnitSteps steps, multi- against single-unit: 32768 tokens, sink 0,
+// window 64 167 and 174 us (32 heads over 8), 156 and 169 (24 over 8), 90 and 95
+// (16 over 2); 128 sequences of 256 tokens, sink 8, window 128 174 and 187, 156
+// and 178, 86 and 89 (28 over 4: 159 and 183); 65536 tokens, sink 64, window
+// 128 397 and 408, 346 and 355, 203 and 210.  A launch of few units per
+// workgroup loses up to 6 % (16384 tokens: 58 and 54 us, 16 over 2; 106 and 107,
+// 32 over 8).  10-12 steps (sink 8, window 512) are 1 % slower, 36 steps (window
+// 2048) 6-10 %.  Groups of 5 and 6, whose row blocks fill eight waves in the
+// single-unit kernel only, stay there (24000 tokens, sink 64, window 128, group
+// 6: 282 us in units of six waves, 241 without), and so does d = 64, whose
+// single-unit kernel runs three four-wave workgroups to a CU (65536 tokens, sink
+// 64, window 128, 32 over 8: 285 us in units, 240 without; 12 to 31 % over 20
+// shapes).  For short units: one workgroup per CU (256 CUs over the kv
 // heads) when its units' steps fit the LDS step table, otherwise the fewest
 // rounds of such workgroups whose units fit.  The environment variable
 // TRIATTN_UNITS_PER_WG, read at every launch, overrides the count (1: the
 // single-unit kernel) within the table limits: for tests and tuning.
 constexpr int64_t kShortUnitSteps = 8;
-int units_per_wg(const FwdArgs &a, int kind, int nw, int64_t units, int32_t max_item_tiles)
+int units_per_wg(const FwdArgs &a, int kind, int head_dim, int nw, int64_t units,
+                 int32_t max_item_tiles)
 {
-    if (kind != TA_KIND_TRIANGLE || nw < 6 || a.group == 6 || units > INT32_MAX ||
+    if (kind != TA_KIND_TRIANGLE || head_dim != 128 || nw < 6 || a.group == 6 || units > INT32_MAX ||
         a.total_tokens >= kMaxUnitsTokens || max_item_tiles < 1)
         return 1;
     const int64_t unit_steps = (int64_t)max_item_tiles * (a.tile / kStep);
@@ -2626,15 +2632,14 @@ ta_status launch_tiles(const char *fn, int kind, const FwdArgs &a_in, int32_t he
     hipError_t err;
     // Triangle passes over workgroups of six to eight waves run several
     // units per workgroup (multi-unit kernel); the others one.
-    const int upw = units_per_wg(a, kind, units_nw, units, info->max_item_tiles);
+    const int upw = units_per_wg(a, kind, head_dim, units_nw, units, info->max_item_tiles);
     if (upw > 1) {
         a.subtiles = units_subtiles;
         a.n_units = (int32_t)units;
         a.upw = upw;
         a.n_slots = (int32_t)((units + upw - 1) / upw);
         dim3 grid((unsigned)((int64_t)a.n_slots * a.hkv));
-        err = head_dim == 128 ? launch_units<128>(units_nw, grid, a, kind, stream)
-                              : launch_units<64>(units_nw, grid, a, kind, stream);
+        err = launch_units<128>(units_nw, grid, a, kind, stream);
     } else {
         // (more than check_common counted where d = 64 takes smaller workgroups)
         const int64_t wgs = (int64_t)a.n_items * a.subtiles * a.hkv;

@@ -27,11 +27,11 @@ ENV = "TRIATTN_UNITS_PER_WG"
 CASES = [
     # cu, hq, hkv, d, S, W, L, T, splits
     ([0, 1500], 16, 2, 128, 1, 1, 1, 128, 0),                      # G 8, 2-key rows
-    ([0, 0, 100, 100, 357, 1000], 8, 2, 64, 3, 50, 77, 64, 0),     # G 4, packed, empty
+    ([0, 0, 100, 100, 357, 1000], 8, 2, 128, 3, 50, 77, 64, 0),    # G 4, packed, empty
     ([0, 640], 8, 2, 128, 130, 65, 129, 128, 3),                   # sink not aligned
     ([0, 2000], 28, 4, 128, 16, 100, 40, 128, 0),                  # G 7 (Qwen group)
     ([0, 700, 1300], 6, 2, 128, 8, 64, 200, 64, 5),                # G 3, six waves
-    ([0, 1000], 3, 1, 64, 4, 128, 300, 128, 7),                    # G 3, d 64, six waves
+    ([0, 1000], 3, 1, 128, 4, 128, 300, 128, 7),                   # G 3, T 128, six waves
     ([0, 1000], 8, 2, 128, 16, 128, 200, 128, 8),                  # splits without steps
 ]
 

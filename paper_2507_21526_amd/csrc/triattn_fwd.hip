@@ -332,9 +332,10 @@ constexpr int phase_reads(int i, int count)
 // which some wave's 32 rows keep no key, at the diagonal and at the window's
 // start; that wave's probabilities are 0 there, and 0 times an infinite or NaN
 // V would reach rows that do not see its key, so the wave reads a tile of zeros
-// in place of V in such a step.  A form of its own: it costs 1 to 5 % (24000
-// tokens, window 2048, 40 heads over 8: 996 -> 1029 us; window 512 442 -> 446),
-// which the groups that never straddle do not pay.
+// in place of V in such a step.  A form of its own, whose V offsets are added to
+// in every step (0.5 to 2.4 %: 24000 tokens, window 2048, 40 heads over 8 985 ->
+// 1005 us; a branch around the additions cost 3 to 5 %), which the groups that
+// never straddle do not pay.
 template <int D, int NW, bool COPIER = false, bool LIST = false, bool STRADDLE = false>
 __global__ __launch_bounds__(NW * 64, NW == 4 ? (D == 64 ? 3 : 2) : 1) void attn_tile_kernel(FwdArgs a,
                                                                                int32_t kind)
@@ -360,18 +361,18 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? (D == 64 ? 3 : 2) : 1) void attn
     // row blocks to a workgroup; each K/V tile copied then serves half the
     // rows, which L2 carries.  Eight-wave (group 7: copier) form against it,
     // same outputs bit for bit: window 2048, 65536 tokens, 32 heads over 8
-    // 1421 -> 1363 us; 48000 tokens, 28 over 4 (STRADDLE) 920 -> 891; multi-head
+    // 1421 -> 1363 us; 48000 tokens, 28 over 4 (STRADDLE) 920 -> 864; multi-head
     // 32768 tokens (four waves before, two to a CU) 754 -> 707; window 512, 65536
     // tokens 594 -> 558; causal 8000 tokens, 40 over 8 (STRADDLE; against
-    // workgroups of five waves) 445 -> 345; 32768 tokens, 32 over 8 4363 -> 4347
+    // workgroups of five waves) 445 -> 342; 32768 tokens, 32 over 8 4363 -> 4347
     // (of many steps each: even).
     constexpr bool LEAN = D == 64 && NW == 4;
     // An item's row blocks (32 rows of one head) are dealt out head first
     // (block b: head b % G, rows 32 (b / G)..), blocks_per_wg to a workgroup,
     // by the eight-wave and the d = 64 four-wave form, so that they serve any
     // group: groups of 5 and 6 take three workgroups of a 128-row tile instead of
-    // four of five or six waves (24000 tokens, window 2048: 1197 to 1029 and
-    // 1306 to 1149 us, STRADDLE included).  The other forms take R rows of every
+    // four of five or six waves (24000 tokens, window 2048: 1197 to 1005 and
+    // 1306 to 1120 us, STRADDLE included).  The other forms take R rows of every
     // head.
     constexpr bool BLOCKS = LEAN || (NW == 8 && !COPIER);
     constexpr int N_COPY_WAVES = COPIER ? 1 : NW - NW / 2;
@@ -976,6 +977,7 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? (D == 64 ? 3 : 2) : 1) void attn
     f32x16 s_acc[2];
     bf16x8 p_acc[2][2];
     bool dead = false;  // the wave's rows keep no key of the last softmax's step
+    uint32_t vshift = 0;  // how far voff is moved off V
 
     // Matrix phase: QK^T of step j (if any) and PV of step j-1 (if any).
     // Inside the step loops (unrolled by two) the LDS stage is a
@@ -991,12 +993,13 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? (D == 64 ? 3 : 2) : 1) void attn
         __builtin_amdgcn_sched_barrier(0);
         prep();
         const int buf = stage;
-        // from this stage's V tile to the zeros
-        const uint32_t to_zeros = (uint32_t)(ZREGION - TILE_BYTES - buf * STAGE_BYTES);
-        if (STRADDLE && has_pv && __builtin_expect(dead, 0)) {
+        if (STRADDLE && has_pv) {
+            // V of this stage, or the zeros: the offsets move by the change
+            const uint32_t to = dead ? (uint32_t)(ZREGION - TILE_BYTES - buf * STAGE_BYTES) : 0u;
 #pragma unroll
             for (int b = 0; b < D_BLOCKS; ++b)
-                voff[b] += to_zeros;
+                voff[b] += to - vshift;
+            vshift = to;
         }
         if (!COPIER && has_qk && has_pv) {
             qk(buf, s_acc, hook, pre, std::false_type{});
@@ -1008,11 +1011,6 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? (D == 64 ? 3 : 2) : 1) void attn
             if (has_pv)
                 pv(buf, p_acc, hook, std::true_type{});
         }
-        if (STRADDLE && has_pv && __builtin_expect(dead, 0)) {
-#pragma unroll
-            for (int b = 0; b < D_BLOCKS; ++b)
-                voff[b] -= to_zeros;
-        }
         __builtin_amdgcn_sched_barrier(0);
         __builtin_amdgcn_s_setprio(0);
         __builtin_amdgcn_sched_barrier(0);
@@ -1023,14 +1021,12 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? (D == 64 ? 3 : 2) : 1) void attn
         const bool need_causal = key0 + kStep - 1 > row_base;
         const bool need_window = mode == kModeStreaming && key0 + kStep - 1 >= a.sink &&
                                  row_hi - key0 >= a.window;
-        dead = false;
-        if (__builtin_expect(need_causal | need_window, 0)) {  // a few steps per item
+        if (__builtin_expect(need_causal | need_window, 0))  // a few steps per item
             mask_step(key0, need_causal, need_window, s_acc);
-            if constexpr (STRADDLE)  // (list schedules have no streaming rows)
-                dead = __builtin_amdgcn_readfirstlane(key0) > row_hi ||
-                       (!LIST && need_window && key0 >= a.sink &&
-                        row_base - (key0 + kStep - 1) >= a.window);
-        }
+        if constexpr (STRADDLE)  // (list schedules have no streaming rows)
+            dead = (__builtin_amdgcn_readfirstlane(key0) > row_hi) |
+                   (!LIST & (mode == kModeStreaming) & (key0 >= a.sink) &
+                    (row_base - (key0 + kStep - 1) >= a.window));
         softmax(s_acc, p_acc);
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb)

@@ -10,9 +10,10 @@
 // weights (Appendix A.1, merge of the last-row buffers).
 //
 // Tile core (flash-style online softmax, Sec. 2.1 evaluated blockwise):
-//   A workgroup owns one work item, one kv head g and R query rows of each of
-//   the G query heads of g, so every K/V tile staged in LDS is shared by the
-//   whole GQA group.  Each wave owns 32 query rows of one head.  Keys advance
+//   A workgroup owns one work item, one kv head g and row blocks of the G
+//   query heads of g, 32 query rows of one head to a wave (R rows of every
+//   head, or blocks dealt out head first: see BLOCKS), so every K/V tile staged
+//   in LDS is shared by them all.  Keys advance
 //   in steps of 64.  The wave computes S^T = K Q^T with bf16 MFMA 32x32x16
 //   (keys on the MFMA rows, queries on the columns), so a lane holds 32
 //   scores of a single query: the softmax max/sum are in-lane plus one swap

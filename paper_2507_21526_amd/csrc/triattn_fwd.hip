@@ -79,6 +79,7 @@ struct FwdArgs {
     int32_t rows_per_wg;  // R
     int32_t subtiles;     // workgroups per item and kv head
     int32_t blocks_per_wg;  // row blocks per workgroup where they are dealt out
+    uint32_t group_inv;   // 65536 / group + 1: x * group_inv >> 16 = x / group, x < 4096
     int32_t o_f32;
     float scale_log2;     // softmax scale * log2(e)
     // multi-unit kernel: units = items x subtiles per kv head; workgroup
@@ -473,8 +474,12 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? (D == 64 ? 3 : 2) : 1) void attn
     const int32_t *tile_list = sched + a.list_base + (list_mode ? ka0 : 0);
     const int max_ktile = seq_len > 0 ? (seq_len - 1) / a.tile : 0;
 
+    // row block b is 32 rows from row 32 (b / group) of head b % group
+    auto block_row = [&](int b) TA_INLINE -> int {
+        return (int)((uint32_t)b * a.group_inv >> 16);
+    };
     const int wr0 =  // first row of this workgroup
-        BLOCKS ? r0 + 32 * (a.blocks_per_wg * sub / a.group) : r0 + sub * a.rows_per_wg;
+        BLOCKS ? r0 + 32 * block_row(a.blocks_per_wg * sub) : r0 + sub * a.rows_per_wg;
     if (wr0 >= r1)
         return;  // ragged q-tile: nothing for this workgroup
 
@@ -488,9 +493,9 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? (D == 64 ? 3 : 2) : 1) void attn
     const int col = lane & 31;
     int head, row_base;
     if constexpr (BLOCKS) {
-        const int b = a.blocks_per_wg * sub + wave;
-        head = g * a.group + b % a.group;
-        row_base = r0 + 32 * (b / a.group);
+        const int b = a.blocks_per_wg * sub + wave, br = block_row(b);
+        head = g * a.group + b - br * a.group;
+        row_base = r0 + 32 * br;
     } else {
         const int waves_per_head = a.rows_per_wg / 32;
         head = g * a.group + wave / waves_per_head;
@@ -507,7 +512,7 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? (D == 64 ? 3 : 2) : 1) void attn
     // to this workgroup's rows (trim_runs).
     const int tps = a.tile / kStep;
     const int wr_last =
-        (BLOCKS ? min(r0 + 32 * ((a.blocks_per_wg * (sub + 1) - 1) / a.group + 1), r1)
+        (BLOCKS ? min(r0 + 32 * (block_row(a.blocks_per_wg * (sub + 1) - 1) + 1), r1)
                 : min(wr0 + a.rows_per_wg, r1)) - 1;
     int a_lo = ka0 * tps, a_hi = ka1 * tps, b_lo = kb0 * tps, b_hi = kb1 * tps;
     if (!list_mode)
@@ -2317,6 +2322,17 @@ int rows_per_wg(int group, int tile)
     return 32;
 }
 
+// Row blocks that fill groups of R rows evenly: the most blocks to a workgroup
+// of nw waves at which none straddles.
+int even_blocks(int group, int nw, int R)
+{
+    const int run = group * (R / 32);
+    int per = std::min(nw, run);
+    while (run % per)
+        --per;
+    return per;
+}
+
 // Whether some workgroup of dealt row blocks (32 rows of each of `group` heads,
 // head first, per_wg to a workgroup) holds blocks of more than one group of
 // R rows, the rows that share a workgroup in the other forms: groups of 5 and 6
@@ -2468,6 +2484,7 @@ FwdArgs make_args(const void *q, const void *k, const void *v, void *o,
     a.rows_per_wg = R;
     a.subtiles = info->tile / R;
     a.blocks_per_wg = 0;
+    a.group_inv = 65536u / (uint32_t)group + 1;
     a.o_f32 = o_dtype == TA_OUT_F32;
     a.scale_log2 = scale * kLog2e;
     a.n_units = 0;
@@ -2623,6 +2640,18 @@ ta_status launch_tiles(const char *fn, int kind, const FwdArgs &a_in, int32_t he
         a.subtiles = (blocks + nw - 1) / nw;
         a.blocks_per_wg = (blocks + a.subtiles - 1) / a.subtiles;
         straddle = straddles(a.group, blocks, a.blocks_per_wg, a.rows_per_wg);
+        // Workgroups that straddle walk more steps, which fewer of them make
+        // good where the launch takes several rounds.  One of a single round is
+        // as long as its longest workgroup (three sequences of 1019 tokens, 5
+        // heads over one kv head, sink 64, window 128: 12.7 us straddling, 10.6
+        // so; d = 64, 1261 tokens, 3 heads: 10.4 and 8.6).
+        const int per = even_blocks(a.group, nw, a.rows_per_wg);
+        const int64_t even_wgs = (int64_t)a.n_items * (blocks / per) * a.hkv;
+        if (straddle && even_wgs <= (int64_t)tile_cost(lean, nw, per).slots) {
+            a.subtiles = blocks / per;
+            a.blocks_per_wg = per;
+            straddle = false;
+        }
     }
     const int units_nw = a.group * a.rows_per_wg / 32;  // of the multi-unit kernel
     const int64_t units = (int64_t)a.n_items * units_subtiles;

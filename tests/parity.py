@@ -42,6 +42,14 @@ def run_pass(kind, q, k, v, cu, sink, window, last, tile, splits=0,
     return o, lse, plan
 
 
+def kernels_of(call):
+    """Names of the kernels that the call launches."""
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as prof:
+        call()
+        torch.cuda.synchronize()
+    return [e.name for e in prof.events()]
+
+
 def boundary_rows(n, sink, window, last, tile):
     lr = min(last, n)
     cand = {0, 1, sink - 1, sink, sink + 1, sink + window - 1, sink + window,

@@ -37,6 +37,16 @@ CASES = [
     ("triangle", 700, 2, 1, 64, 8, 100, 40, 128, (3, 130, 320, 690)),
     ("triangle", 700, 1, 1, 64, 70, 65, 0, 128, (3, 130, 320)),
     ("triangle", 700, 7, 1, 64, 4, 200, 64, 64, (3, 320, 650)),
+    # launches of more than one round, whose workgroups straddle groups of rows
+    ("causal", 1250, 40, 8, 128, 0, 1, 0, 128, (70, 1000)),
+    ("causal", 1250, 48, 8, 128, 0, 1, 0, 128, (70, 1000)),
+    ("lists", 1250, 40, 8, 128, 0, 1, 0, 128, (70, 1000)),
+    ("triangle", 1250, 40, 8, 128, 0, 130, 0, 128, (60, 200, 830)),
+    ("triangle", 1250, 48, 8, 128, 8, 200, 40, 128, (3, 830, 1240)),
+    ("causal", 700, 56, 8, 64, 0, 1, 0, 128, (70, 430)),
+    ("lists", 700, 56, 8, 64, 0, 1, 0, 128, (70, 430)),
+    ("triangle", 3300, 24, 8, 64, 8, 130, 40, 128, (3, 1700, 3290)),
+    ("triangle", 800, 40, 8, 64, 4, 200, 64, 64, (3, 320, 750)),
 ]
 
 

@@ -13,7 +13,7 @@ import torch
 
 from paper_2507_21526_amd import binding
 from paper_2507_21526_amd.inputs import draw_qkv
-from tests.parity import compare, log, run_pass
+from tests.parity import compare, kernels_of, log, run_pass
 
 pytestmark = pytest.mark.gpu
 
@@ -39,6 +39,16 @@ CASES = [
     ("triangle", [0, 700], 3, 3, 64, 0, 65, 40, 128, 0),          # G 1: 128 rows of a head
 ]
 
+# launches of more than one round, whose workgroups' blocks straddle groups of
+# rows
+STRADDLE_CASES = [
+    ("causal", [0, 300, 1200], 40, 8, 128, 0, 1, 0, 128, 0),       # G 5: 7, 7 and 6 blocks
+    ("triangle", [0, 1250], 48, 8, 128, 8, 130, 40, 128, 0),       # G 6: 8, 8 and 8
+    ("triangle", [0, 33, 750], 56, 8, 64, 8, 130, 70, 128, 2),     # G 7
+    ("causal", [0, 333, 850], 40, 8, 64, 0, 1, 0, 128, 0),         # G 5, d 64
+    ("triangle", [0, 3333], 24, 8, 64, 0, 130, 70, 128, 0),        # G 3, no sink
+]
+
 
 def _run(*args, **kw):
     o, lse, _ = run_pass(*args, poison=True, **kw)
@@ -49,14 +59,36 @@ def _run(*args, **kw):
 @pytest.mark.parametrize("kind,cu,hq,hkv,d,S,W,L,T,splits", CASES)
 def test_row_blocks(kind, cu, hq, hkv, d, S, W, L, T, splits):
     log(f"case row blocks {kind} cu={cu} hq={hq} hkv={hkv} d={d} S={S} W={W} L={L} T={T}")
+    _check_rows(kind, cu, hq, hkv, d, S, W, L, T, splits, range(hq))
+
+
+@pytest.mark.parametrize("kind,cu,hq,hkv,d,S,W,L,T,splits", STRADDLE_CASES)
+def test_straddling_row_blocks(kind, cu, hq, hkv, d, S, W, L, T, splits):
+    log(f"case straddling {kind} cu={cu} hq={hq} hkv={hkv} d={d} S={S} W={W} L={L} T={T}")
+    g = hq // hkv
+    args = _check_rows(kind, cu, hq, hkv, d, S, W, L, T, splits,
+                       [*range(g), *range(hq - g, hq)])
+    names = [n for n in kernels_of(lambda: _run(*args)) if "attn_tile_kernel" in n]
+    assert len(names) == 1 and "false, false, true>" in names[0], names
+    # the first kv head alone, in a launch of one round whose workgroups do not
+    o, lse = _run(*args)
+    one = [args[0], args[1][:, :g].contiguous()] + [t[:, :1].contiguous() for t in args[2:4]]
+    names = [n for n in kernels_of(lambda: _run(*one, *args[4:])) if "attn_tile_kernel" in n]
+    assert len(names) == 1 and "false, false, false>" in names[0], names
+    o1, lse1 = _run(*one, *args[4:])
+    assert torch.equal(o[:, :g], o1) and torch.equal(lse[:g], lse1)
+
+
+def _check_rows(kind, cu, hq, hkv, d, S, W, L, T, splits, heads):
     q, k, v = draw_qkv(cu, hq, hkv, d, seed=31 + hq + S)
     args = [kind] + [t.cuda() for t in (q, k, v)] + [cu, S, W, L, T, splits]
     o, lse = _run(*args)
     assert not torch.isnan(o).any() and not torch.isnan(lse).any()
     compare(kind, q, k, v, cu, S, W, L, 1 / math.sqrt(d), o, lse, np.arange(cu[-1]),
-            range(hq), label=f"{kind} cu={cu}", p_bound=True)
+            heads, label=f"{kind} cu={cu}", p_bound=True)
     o16, _ = _run(*args, out_dtype=torch.bfloat16)
     assert torch.equal(o16, o.bfloat16())
+    return args
 
 
 @pytest.mark.parametrize("hq,d,T,bound", [(5, 128, 128, 0), (3, 64, 64, 3)])

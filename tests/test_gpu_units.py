@@ -18,7 +18,7 @@ import pytest
 import torch
 
 from paper_2507_21526_amd.inputs import draw_qkv
-from tests.parity import compare, log, run_pass
+from tests.parity import compare, kernels_of, log, run_pass
 
 pytestmark = pytest.mark.gpu
 
@@ -47,14 +47,6 @@ def _run(kind, q, k, v, cu, S, W, L, T, splits, upw, out_dtype):
     return o, lse
 
 
-def _kernels(call):
-    """Names of the kernels that the call launches."""
-    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as prof:
-        call()
-        torch.cuda.synchronize()
-    return [e.name for e in prof.events()]
-
-
 @pytest.mark.parametrize("cu,hq,hkv,d,S,W,L,T,splits", CASES)
 def test_units_bit_identical_to_single_unit(cu, hq, hkv, d, S, W, L, T, splits):
     log(f"case units cu={cu} hq={hq} hkv={hkv} d={d} S={S} W={W} L={L} T={T} splits={splits}")
@@ -64,8 +56,8 @@ def test_units_bit_identical_to_single_unit(cu, hq, hkv, d, S, W, L, T, splits):
         assert not torch.isnan(ref_o).any()
         for upw in (2, 3, 7, 128):
             if out_dtype == torch.float32:
-                names = _kernels(lambda: _run("triangle", q, k, v, cu, S, W, L, T, splits, upw,
-                                              out_dtype))
+                names = kernels_of(lambda: _run("triangle", q, k, v, cu, S, W, L, T, splits,
+                                                upw, out_dtype))
                 assert any("attn_units_kernel" in n for n in names), (upw, names)
                 assert not any("attn_tile_kernel" in n for n in names), (upw, names)
             o, lse = _run("triangle", q, k, v, cu, S, W, L, T, splits, upw, out_dtype)
@@ -105,7 +97,7 @@ def test_units_noalloc_and_graph_replay():
     finally:
         del os.environ[ENV]
     assert torch.equal(ref, single)
-    names = _kernels(lambda: plan.run(q, k, v, single, None, d ** -0.5))
+    names = kernels_of(lambda: plan.run(q, k, v, single, None, d ** -0.5))
     assert any("attn_units_kernel" in n for n in names), names
     na = torch.empty_like(ref)
     binding.triangle_attn_fwd_noalloc(q, k, v, na, None, plan.sched, plan.info, d ** -0.5)

@@ -2364,17 +2364,18 @@ hipError_t launch_tile_as(int nw, bool straddle, dim3 grid, const FwdArgs &a, in
         if constexpr (D == 128)
             hipLaunchKernelGGL((attn_tile_kernel<D, 8, true, LIST>), grid, dim3(512), 0, s, a, kind);
         else
-            return hipErrorInvalidValue;  // d = 64 runs four waves
+            return hipErrorInvalidValue;  // no copier wave at d = 64
         break;
     case 8:
-        if constexpr (D == 128) {
-            if (straddle)
+        if constexpr (D == 128)
+            if (straddle) {
                 hipLaunchKernelGGL((attn_tile_kernel<D, 8, false, LIST, true>), grid, dim3(512), 0, s, a, kind);
-            else
-                hipLaunchKernelGGL((attn_tile_kernel<D, 8, false, LIST>), grid, dim3(512), 0, s, a, kind);
-        } else {
+                break;
+            }
+        if constexpr (D == 128 || !LIST)
+            hipLaunchKernelGGL((attn_tile_kernel<D, 8, false, LIST>), grid, dim3(512), 0, s, a, kind);
+        else
             return hipErrorInvalidValue;
-        }
         break;
     default: return hipErrorInvalidValue;
     }
@@ -2618,6 +2619,26 @@ int units_per_wg(const FwdArgs &a, int kind, int head_dim, int nw, int64_t units
     }
 }
 
+// Whether a dense causal pass at d = 64 runs eight-wave workgroups after all:
+// where its four-wave ones would take a little more than one round of three to
+// a CU while eight-wave ones fill at most two rounds of one.  Both end with
+// the longest rows' workgroups, which three to a CU slow down.  Lean against
+// eight waves: 31179 tokens, 4 heads over one kv head (976 workgroups) 549 and 501
+// us, 16000 tokens, 8 over 1 (1000) 289 and 267, 7 over 1 (875) 267 and 245, 8192
+// tokens, 16 over 4 (1024) 155 and 144; outside, lean is ahead: 752 workgroups 179
+// and 183, 500 195 and 222, 1252 423 and 436, 1504 604 and 629; even at 816.  Groups
+// of 5 and 6, whose eight waves straddle, stay lean, as do Triangle and
+// block-sparse passes, whose items differ less in length.
+bool eight_at_d64(int kind, const FwdArgs &a, int blocks)
+{
+    if (kind != TA_KIND_CAUSAL || blocks < 8)
+        return false;
+    const int per = (blocks + (blocks + 7) / 8 - 1) / ((blocks + 7) / 8);
+    const int64_t rows = (int64_t)a.n_items * a.hkv;
+    return rows * ((blocks + 3) / 4) > 768 && rows * ((blocks + 7) / 8) <= 512 &&
+           !straddles(a.group, blocks, per, a.rows_per_wg);
+}
+
 ta_status launch_tiles(const char *fn, int kind, const FwdArgs &a_in, int32_t head_dim,
                        const ta_schedule_info *info, hipStream_t stream)
 {
@@ -2628,12 +2649,12 @@ ta_status launch_tiles(const char *fn, int kind, const FwdArgs &a_in, int32_t he
     // group 2 at 64-row tiles) fit one workgroup of so many waves, two to a
     // CU; group 7 leaves the eighth wave to copy; all others take eight, the
     // row blocks shared out evenly (a second workgroup of two blocks would
-    // take as long as one of eight).  At d = 64 all take four, three
-    // workgroups to a CU (up to 8 % faster at group 4, 24 % at group 5; group
+    // take as long as one of eight).  At d = 64 all take four (but see
+    // eight_at_d64), three workgroups to a CU (up to 8 % faster at group 4, 24 % at group 5; group
     // 7 at 64-row tiles, whose 14 blocks leave two waves idle, is even).
     const int blocks = a.group * (a.tile / 32);
-    const bool lean = head_dim == 64 && blocks >= 4;
-    const int nw = lean ? 4 : blocks <= 4 ? blocks : a.group == 7 ? 7 : 8;
+    const bool lean = head_dim == 64 && blocks >= 4 && !eight_at_d64(kind, a, blocks);
+    const int nw = lean ? 4 : blocks <= 4 ? blocks : a.group == 7 && head_dim == 128 ? 7 : 8;
     const int units_subtiles = a.subtiles;  // of the multi-unit kernel
     bool straddle = false;
     if (lean || nw == 8) {

@@ -62,19 +62,30 @@ def test_row_blocks(kind, cu, hq, hkv, d, S, W, L, T, splits):
     _check_rows(kind, cu, hq, hkv, d, S, W, L, T, splits, range(hq))
 
 
-@pytest.mark.parametrize("kind,cu,hq,hkv,d,S,W,L,T,splits", STRADDLE_CASES)
-def test_straddling_row_blocks(kind, cu, hq, hkv, d, S, W, L, T, splits):
-    log(f"case straddling {kind} cu={cu} hq={hq} hkv={hkv} d={d} S={S} W={W} L={L} T={T}")
+# dense causal launches at d 64 of 769 to 1024 four-wave workgroups, which run
+# eight-wave ones
+EIGHT_CASES = [
+    ("causal", [0, 1201, 1700], 64, 8, 64, 0, 1, 0, 128, 0),   # G 8: 14 items of 32 blocks
+    ("causal", [0, 1999], 56, 8, 64, 0, 1, 0, 128, 0),         # G 7: 16 items, 7 blocks each
+    ("causal", [0, 3201], 32, 8, 64, 0, 1, 0, 64, 0),          # G 4, T 64: 51 items
+]
+
+
+@pytest.mark.parametrize("form,kind,cu,hq,hkv,d,S,W,L,T,splits", [
+    *(("false, false, true>", *c) for c in STRADDLE_CASES),
+    *(("<64, 8, false, false, false>", *c) for c in EIGHT_CASES)])
+def test_forms_of_larger_launches(form, kind, cu, hq, hkv, d, S, W, L, T, splits):
+    log(f"case larger launch {kind} cu={cu} hq={hq} hkv={hkv} d={d} S={S} W={W} L={L} T={T}")
     g = hq // hkv
     args = _check_rows(kind, cu, hq, hkv, d, S, W, L, T, splits,
                        [*range(g), *range(hq - g, hq)])
     names = [n for n in kernels_of(lambda: _run(*args)) if "attn_tile_kernel" in n]
-    assert len(names) == 1 and "false, false, true>" in names[0], names
-    # the first kv head alone, in a launch of one round whose workgroups do not
+    assert len(names) == 1 and form in names[0], names
+    # the first kv head alone: a launch of one round, in another form
     o, lse = _run(*args)
     one = [args[0], args[1][:, :g].contiguous()] + [t[:, :1].contiguous() for t in args[2:4]]
     names = [n for n in kernels_of(lambda: _run(*one, *args[4:])) if "attn_tile_kernel" in n]
-    assert len(names) == 1 and "false, false, false>" in names[0], names
+    assert len(names) == 1 and form not in names[0], names
     o1, lse1 = _run(*one, *args[4:])
     assert torch.equal(o[:, :g], o1) and torch.equal(lse[:g], lse1)
 

@@ -2619,24 +2619,37 @@ int units_per_wg(const FwdArgs &a, int kind, int head_dim, int nw, int64_t units
     }
 }
 
-// Whether a dense causal pass at d = 64 runs eight-wave workgroups after all:
-// where its four-wave ones would take a little more than one round of three to
-// a CU while eight-wave ones fill at most two rounds of one.  Both end with
-// the longest rows' workgroups, which three to a CU slow down.  Lean against
-// eight waves: 31179 tokens, 4 heads over one kv head (976 workgroups) 549 and 501
-// us, 16000 tokens, 8 over 1 (1000) 289 and 267, 7 over 1 (875) 267 and 245, 8192
-// tokens, 16 over 4 (1024) 155 and 144; outside, lean is ahead: 752 workgroups 179
-// and 183, 500 195 and 222, 1252 423 and 436, 1504 604 and 629; even at 816.  Groups
-// of 5 and 6, whose eight waves straddle, stay lean, as do Triangle and
-// block-sparse passes, whose items differ less in length.
-bool eight_at_d64(int kind, const FwdArgs &a, int blocks)
+// Whether a pass at d = 64 runs eight-wave workgroups after all.  Three four-wave
+// ones to a CU slow each other's steps, which shows where the launch is as long
+// as its longest workgroups:
+//   * dense causal, where the lean workgroups take a little more than one round
+//     of three to a CU and eight-wave ones at most two rounds of one (it ends
+//     with the longest rows).  Lean against eight waves: 31179 tokens, 4 heads
+//     over one kv head (976 workgroups) 549 and 501 us, 16000 tokens, 8 over 1
+//     (1000) 289 and 267, 7 over 1 (875) 267 and 245, 8192 tokens, 16 over 4
+//     (1024) 155 and 144; even at 816; outside lean is ahead: 752 workgroups 179
+//     and 183, 500 195 and 222, 1252 423 and 436.  Groups of 5 and 6, whose eight
+//     waves straddle, stay lean.
+//   * Triangle passes without Last rows (items of one length), where eight-wave
+//     workgroups have a CU each and lean ones share some: 266 lean workgroups
+//     12.5 and 10.5 us, 300 16.6 and 15.3, 344 17.5 and 14.6, 408 12.1 and 11.3;
+//     outside lean is ahead: 248 9.8 and 10.5, 480 19.8 and 24.2.
+// Other passes are faster lean throughout.
+bool eight_at_d64(int kind, const FwdArgs &a, int blocks, const ta_schedule_info *info)
 {
-    if (kind != TA_KIND_CAUSAL || blocks < 8)
+    if (blocks < 5)
         return false;
-    const int per = (blocks + (blocks + 7) / 8 - 1) / ((blocks + 7) / 8);
+    int subs = (blocks + 7) / 8;
+    const bool straddle = straddles(a.group, blocks, (blocks + subs - 1) / subs, a.rows_per_wg);
+    if (straddle)
+        subs = blocks / even_blocks(a.group, 8, a.rows_per_wg);
     const int64_t rows = (int64_t)a.n_items * a.hkv;
-    return rows * ((blocks + 3) / 4) > 768 && rows * ((blocks + 7) / 8) <= 512 &&
-           !straddles(a.group, blocks, per, a.rows_per_wg);
+    const int64_t lean = rows * ((blocks + 3) / 4), eight = rows * subs;
+    if (kind == TA_KIND_CAUSAL)
+        return blocks >= 8 && !straddle && lean > 768 && eight <= 512;
+    return kind == TA_KIND_TRIANGLE && info->n_last_items == 0 && lean > 256 && lean <= 448 &&
+           eight <= 256 &&
+           10 * (int64_t)info->max_item_tiles * a.n_items <= 13 * info->kept_tiles_per_qhead;
 }
 
 ta_status launch_tiles(const char *fn, int kind, const FwdArgs &a_in, int32_t head_dim,
@@ -2653,7 +2666,7 @@ ta_status launch_tiles(const char *fn, int kind, const FwdArgs &a_in, int32_t he
     // eight_at_d64), three workgroups to a CU (up to 8 % faster at group 4, 24 % at group 5; group
     // 7 at 64-row tiles, whose 14 blocks leave two waves idle, is even).
     const int blocks = a.group * (a.tile / 32);
-    const bool lean = head_dim == 64 && blocks >= 4 && !eight_at_d64(kind, a, blocks);
+    const bool lean = head_dim == 64 && blocks >= 4 && !eight_at_d64(kind, a, blocks, info);
     const int nw = lean ? 4 : blocks <= 4 ? blocks : a.group == 7 && head_dim == 128 ? 7 : 8;
     const int units_subtiles = a.subtiles;  // of the multi-unit kernel
     bool straddle = false;

@@ -62,12 +62,14 @@ def test_row_blocks(kind, cu, hq, hkv, d, S, W, L, T, splits):
     _check_rows(kind, cu, hq, hkv, d, S, W, L, T, splits, range(hq))
 
 
-# dense causal launches at d 64 of 769 to 1024 four-wave workgroups, which run
-# eight-wave ones
+# launches at d 64 that run eight-wave workgroups: dense causal ones of 769 to
+# 1024 four-wave workgroups, Triangle ones without Last rows of 257 to 448
 EIGHT_CASES = [
     ("causal", [0, 1201, 1700], 64, 8, 64, 0, 1, 0, 128, 0),   # G 8: 14 items of 32 blocks
     ("causal", [0, 1999], 56, 8, 64, 0, 1, 0, 128, 0),         # G 7: 16 items, 7 blocks each
     ("causal", [0, 3201], 32, 8, 64, 0, 1, 0, 64, 0),          # G 4, T 64: 51 items
+    ("triangle", [0, 1150], 32, 4, 64, 0, 128, 0, 128, 0),     # G 8: 9 items
+    ("triangle", [0, 2500], 15, 3, 64, 8, 128, 0, 128, 0),     # G 5: 20 items, 5 blocks each
 ]
 
 
